@@ -102,6 +102,56 @@ void choose_conv_tile(int64_t M, int Kp, int Kg, ConvTile* t, int* splits, int* 
   }
 }
 
+// Launches with more 64x64 tiles than CUs (choose_conv_tile's plain 64x64
+// case): the tile whose modelled time is least.  A tile's workgroups run in
+// rounds of occ per CU; a round costs a fixed part (prologue, first fills,
+// epilogue, drain) and, per 64-deep stage, the time of as many co-resident
+// workgroups as its CUs hold.  The numbers are us measured on MI355X over dense layers
+// of 784-50176 rows, 256-3072 channels and reductions of 256-2304, and
+// agree with the measured times to about 10%: 12544 x 1024 x 2304 104 us on
+// 64x64 tiles, 58.7 on 256x256 (modelled 53), 65.9 on 128x128; 6272 x 1024 x 2304
+// 55.8, 51.3 and 35.7; 50176 x 256 x 1024 49.2, 33.2 and 36.8.  A GELU
+// epilogue adds its vector-ALU time, which a single workgroup per CU cannot overlap.
+struct PipeCost {
+  int bm, bn, threads, stages, occ;
+  double fixed, stage[3], gelu;
+};
+constexpr PipeCost kPipeCost[] = {
+    {256, 256, 512, 2, 1, 8.0, {1.25}, 12.0},          {256, 128, 512, 3, 1, 6.8, {0.77}, 6.0},
+    {128, 256, 512, 3, 1, 6.5, {0.76}, 6.0},           {128, 192, 512, 3, 1, 6.5, {0.62}, 4.5},
+    {128, 128, 512, 2, 2, 6.0, {0.36, 0.74}, 4.0},     {128, 64, 256, 3, 2, 5.0, {0.33, 0.53}, 1.5},
+    {64, 128, 256, 3, 2, 5.0, {0.31, 0.53}, 1.5},      {64, 64, 256, 3, 3, 4.5, {0.23, 0.34, 0.48}, 1.0},
+};
+// (the windowed 3x3 kernel's 128x64 tile, one workgroup per CU)
+constexpr PipeCost kHaloCost = {128, 64, 512, 3, 1, 3.0, {0.24}, 1.5};
+
+double tile_cost(const PipeCost& c, const ConvParams& p) {
+  constexpr int kCus = 256;
+  const int64_t tiles = ((p.M + c.bm - 1) / c.bm) * (int64_t)((p.Kp + c.bn - 1) / c.bn);
+  const int st = (p.Kg + kKPad - 1) / kKPad;
+  const double fixed = c.fixed + (p.act == kActGelu ? c.gelu : 0.0);
+  const int64_t full = tiles / (kCus * c.occ), rest = tiles % (kCus * c.occ);
+  double t = (double)full * (fixed + st * c.stage[c.occ - 1]);
+  if (rest > 0) t += fixed + st * c.stage[(rest + kCus - 1) / kCus - 1];
+  return t;
+}
+
+double choose_pipe_tile(const ConvParams& p, ConvTile* t) {
+  double best = 0.0;
+  for (const PipeCost& c : kPipeCost) {
+    const double v = tile_cost(c, p);
+    if (best > 0.0 && v >= best) continue;
+    best = v;
+    *t = ConvTile{};
+    t->bm = c.bm;
+    t->bn = c.bn;
+    t->stages = c.stages;
+    t->threads = c.threads;
+    t->pipe = 1;
+  }
+  return best;
+}
+
 // Tuning override (environment, read at engine creation):
 // BYOC_CONV_TILE=<bm>x<bn>[x<mfma 16|32>] (register-staged) or d<bm>x<bn>s<stages>
 // (HBM->LDS pipeline) forces a compiled tile, BYOC_CONV_SPLIT=<n> a
@@ -127,6 +177,18 @@ void apply_tile_override(int Kg, ConvTile* t, int* splits, int* kps) {
         t->threads = 512;
         t->kgroups = 1;
         t->halo = 2;  // requested; resolved against the shape by the planner
+      }
+    } else if (e[0] == 'p') {
+      // p<bm>x<bn>s<stages>t<threads>: conv_pipe kernel (convs it takes; others keep their tile)
+      int nt = 512;
+      if (std::sscanf(e + 1, "%dx%ds%dt%d", &bm, &bn, &ns, &nt) >= 3 && conv_pipe_tile_supported(bm, bn, ns, nt)) {
+        t->bm = bm;
+        t->bn = bn;
+        t->mf = 16;
+        t->stages = ns;
+        t->threads = nt;
+        t->kgroups = 1;
+        t->pipe = 2;  // requested; resolved against the shape by the planner
       }
     } else if (e[0] == 'd') {
       // d<bm>x<bn>s<stages>[t<threads>[k<groups>]]: direct HBM->LDS pipeline
@@ -201,6 +263,9 @@ void name_conv(Launch& L) {
   if (L.tile.halo)
     std::snprintf(L.info.name, sizeof(L.info.name), "conv_halo_%dx%d_s%d_lp%d_pb%d", L.tile.bm, L.tile.bn,
                   L.tile.stages, L.tile.lp, L.tile.npb);
+  else if (L.tile.pipe)
+    std::snprintf(L.info.name, sizeof(L.info.name), "conv_pipe_%dx%d_s%d_w%d", L.tile.bm, L.tile.bn, L.tile.stages,
+                  L.tile.threads / 64);
   else if (L.tile.stages > 0)
     std::snprintf(L.info.name, sizeof(L.info.name), "conv_dma_%dx%d_s%d_w%d_k%d_split%d", L.tile.bm, L.tile.bn,
                   L.tile.stages, L.tile.threads / 64, L.tile.kgroups, L.conv.splits);
@@ -1212,28 +1277,52 @@ void Planner::plan_node(int ni) {
     int splits, kps;
     choose_conv_tile(p.M, Kp, p.Kg, &L.tile, &splits, &kps);
     apply_tile_override(p.Kg, &L.tile, &splits, &kps);
+    if (L.tile.pipe == 2) {  // a forced conv_pipe tile forgoes split-K
+      ConvParams q = p;
+      q.splits = 1;
+      if (conv_pipe_ok(q)) {
+        L.tile.pipe = 1;
+        splits = 1;
+        kps = (p.Kg + kKPad - 1) / kKPad;
+      } else {
+        L.tile = ConvTile{};
+        choose_conv_tile(p.M, Kp, p.Kg, &L.tile, &splits, &kps);
+      }
+    }
     p.splits = splits;
     p.k_tiles_per_split = kps;
     {
-      // 3x3 stride-1 convs with at least 256 input channels and enough
-      // 128x64 tiles to fill most CUs run on the halo kernel (input window
-      // staged in LDS once per 64-channel slice).  Measured on MI355X over
-      // the ResNet-50 layers at batch 32: it wins on 256 channels at 14x14
-      // (196 tiles) and loses where the patch is large against the work
-      // (64 channels at 56x56), where the implicit-GEMM kernel's 128x128
-      // tiles win (128 channels at 28x28) and where 128x64 tiles leave most
-      // CUs idle (512 channels at 7x7, 104 tiles).  Where 128x64 tiles are
-      // too few but 64x64 tiles are enough (512 channels at 7x7: 200 tiles)
-      // it runs on 64x64 tiles.  BYOC_CONV_HALO=1 takes it wherever the
-      // shape allows, =0 never; a forced tile decides alone.
+      // Built-in choice between the kernels.  Many tiles: the cheapest
+      // conv_pipe tile, or for a 3x3 stride-1 conv the windowed kernel
+      // (conv_halo: the input window staged in LDS once per 64-channel slice)
+      // if its modelled time is less - it wins while its 128x64 tiles make about one
+      // round (256 channels at 14x14, batch 32: 196 tiles, 13 against 20 us;
+      // 128 -> 256 channels at 32x32, batch 8: 12.7 against 14.8) and loses
+      // with more (512 channels at 28x28, batch 32: 153 against 113 us).
+      // Where 128x64 tiles are too few for that but 64x64 ones are
+      // enough (512 channels at 7x7: 200 tiles) it runs on 64x64 tiles.
+      // BYOC_CONV_HALO=1 takes the windowed kernel wherever the shape allows,
+      // =0 never; a forced tile decides alone.
       const bool forced = L.tile.halo == 2;
       const char* he = std::getenv("BYOC_CONV_HALO");
+      const bool builtin = !std::getenv("BYOC_CONV_TILE") && !std::getenv("BYOC_CONV_SPLIT");
+      const bool many = builtin && splits == 1 && L.tile.kgroups == 1 && conv_pipe_ok(p) &&
+                        ((p.M + 63) / 64) * (int64_t)((Kp + 63) / 64) > 256;
+      ConvTile pipe{};
+      const double pipe_cost = many ? choose_pipe_tile(p, &pipe) : 0.0;
       const int64_t halo_tiles = ((p.M + 127) / 128) * ((Kp + 63) / 64);
       const int64_t halo64_tiles = ((p.M + 63) / 64) * ((Kp + 63) / 64);
-      const bool by_rule = Cp >= 256 && halo_tiles >= 160;
-      const bool by_rule64 = Cp >= 256 && !by_rule && halo64_tiles >= 160;
-      const bool want =
-          forced || (!std::getenv("BYOC_CONV_TILE") && (he ? he[0] == '1' : by_rule || by_rule64));
+      // (wherever the windowed kernel is the 3x3 layer's kernel by its own
+      // rule, conv_pipe takes over its summation order with it)
+      const bool halo_class = Cp >= 256 && halo_tiles >= 160;
+      const bool by_rule = many ? halo_tiles >= 160 && Cp >= 128 && tile_cost(kHaloCost, p) < pipe_cost : halo_class;
+      const bool by_rule64 = Cp >= 256 && halo_tiles < 160 && halo64_tiles >= 160;
+      const bool want = forced || (!std::getenv("BYOC_CONV_TILE") && (he ? he[0] == '1' : by_rule || by_rule64));
+      if (many) {
+        L.tile = pipe;
+        int hl = 0, hn = 0;
+        p.slice_major = halo_class && !he && conv_halo_plan(p, 128, 64, kHaloStages, &hl, &hn);
+      }
       const int ns = forced ? L.tile.stages : kHaloStages;
       const int hbm = forced ? L.tile.bm : by_rule64 ? 64 : 128;
       int lp = 0, npb = 0;
@@ -1256,6 +1345,7 @@ void Planner::plan_node(int ni) {
         L.tile.halo = 1;
         L.tile.lp = lp;
         L.tile.npb = npb;
+        p.slice_major = 1;  // (its autotune alternatives sum in its order)
       } else if (forced) {
         L.tile = ConvTile{};
         choose_conv_tile(p.M, Kp, p.Kg, &L.tile, &splits, &kps);
@@ -1934,6 +2024,7 @@ hipError_t exec(const Launch& L, const RunCtx& c) {
       p.partial = (float*)c.ptr(L.partial);
       if (L.op == Launch::SplitReduce) return launch_splitk_reduce(p, c.s);
       if (L.tile.halo) return launch_conv_halo(p, L.tile.bm, L.tile.bn, L.tile.stages, L.tile.lp, L.tile.npb, c.s);
+      if (L.tile.pipe) return launch_conv_pipe(p, L.tile.bm, L.tile.bn, L.tile.stages, L.tile.threads, c.s);
       return L.tile.stages > 0
                  ? launch_conv_dma(p, L.tile.bm, L.tile.bn, L.tile.stages, L.tile.threads, L.tile.kgroups, c.s)
                                : launch_conv_mfma(p, L.tile, c.s);
@@ -2381,20 +2472,55 @@ namespace {
 std::vector<ConvTile> conv_candidates(const Launch& L) {
   std::vector<ConvTile> c;
   c.push_back(L.tile_default);
-  if (L.tile_default.halo) {  // the halo kernel: other tiles and weight ring depths (same reduction order)
+  // conv_pipe's tiles that fill at least a third of the CUs (or the smallest)
+  auto pipe_tiles = [&] {
+    const ConvParams& p = L.conv;
+    for (const PipeCost& k : kPipeCost) {
+      if (((int64_t)(p.M + k.bm - 1) / k.bm) * ((p.Kp + k.bn - 1) / k.bn) < 88 && k.bm * k.bn > 64 * 64) continue;
+      if (p.Kp <= 64 && k.bn > 64) continue;
+      ConvTile t;
+      t.bm = k.bm, t.bn = k.bn, t.stages = k.stages, t.threads = k.threads, t.pipe = 1;
+      if (L.tile_default.pipe && t.bm == L.tile_default.bm && t.bn == L.tile_default.bn) continue;
+      c.push_back(t);
+    }
+  };
+  if (L.conv.slice_major) {  // conv_halo's summation order: its tiles and weight ring depths, and conv_pipe's tiles
     for (int bm : {128, 64})
       for (int ns : {2, 3, 4, 6, 8}) {
-        ConvTile t = L.tile_default;
-        if ((bm == t.bm && ns == t.stages) || !conv_halo_plan(L.conv, bm, t.bn, ns, &t.lp, &t.npb)) continue;
-        t.bm = bm;
-        t.stages = ns;
+        ConvTile t = ConvTile{};
+        if (L.tile_default.halo && bm == L.tile_default.bm && ns == L.tile_default.stages) continue;
+        if (!conv_halo_plan(L.conv, bm, 64, ns, &t.lp, &t.npb)) continue;
+        t.bm = bm, t.bn = 64, t.stages = ns, t.threads = 512, t.halo = 1;
         c.push_back(t);
       }
+    if (conv_pipe_ok(L.conv)) pipe_tiles();
     return c;
   }
   if (L.conv.splits > 1 || L.tile_default.mf != 16) return c;
   const ConvParams& p = L.conv;
   const int kgr = L.tile_default.kgroups;  // the reduction order class of the built-in choice
+  if (kgr == 1 && conv_pipe_ok(p)) {
+    // conv_pipe's tiles, the pipelined kernel's that win where an epilogue or
+    // a residual weighs most, and the register-staged kernel: all sum in one order
+    pipe_tiles();
+    struct D {
+      int bm, bn, st, th;
+    };
+    for (const D& d : {D{128, 128, 2, 512}, D{128, 128, 3, 512}, D{128, 128, 1, 512}, D{128, 64, 4, 512}, D{128, 64, 2, 256}, D{64, 64, 2, 256},
+                       D{64, 64, 3, 256}, D{64, 64, 4, 256}, D{64, 128, 2, 256}, D{32, 64, 3, 256}, D{32, 64, 4, 256}}) {
+      if (d.bm == 32 && p.M >= 48) continue;
+      if (d.bn == 128 && p.Kp < 128) continue;
+      ConvTile t;
+      t.bm = d.bm, t.bn = d.bn, t.stages = d.st, t.threads = d.th;
+      c.push_back(t);
+    }
+    if (L.tile_default.stages > 0) {
+      ConvTile t;
+      t.bm = p.M >= 48 ? 64 : 32, t.bn = 64;
+      c.push_back(t);
+    }
+    return c;
+  }
   const int bms[] = {32, 64, 128, 256}, bns[] = {64, 128, 256};
   for (int nt : {256, 512})
     for (int bm : bms)

@@ -38,6 +38,7 @@ struct ConvParams {
   int w_bytes;
   int res_bytes;
   int res_post;  // 1: the residual is added after the activation, to its bf16-rounded value
+  int slice_major;  // conv_pipe: 1 sums 64-channel slices outermost, taps inside (conv_halo's order), 0 taps outermost
   // conv_dma tile placement: > 0 splits the tile grid into (8 / xcd_py) x
   // xcd_py blocks along (pixels, channels), one per XCD, so that an XCD's L2
   // holds only its share of both operands; 0 deals tiles out linearly.
@@ -62,6 +63,7 @@ struct ConvTile {
   int halo = 0;       // 1: conv_halo kernel (stages = weight ring depth, lp / npb as planned)
   int lp = 0, npb = 0;
   int bnv = -1;       // fused bottleneck block: the kernel variant
+  int pipe = 0;       // 1: conv_pipe kernel (stages = ring depth, threads 256 or 512)
 };
 
 // Tile configurations with a compiled kernel.
@@ -71,6 +73,13 @@ hipError_t launch_conv_mfma(const ConvParams& p, ConvTile t, hipStream_t s);
 bool conv_dma_tile_supported(int bm, int bn, int stages, int threads, int kgroups);
 hipError_t launch_conv_dma(const ConvParams& p, int bm, int bn, int stages, int threads, int kgroups,
                            hipStream_t s);
+// Large-tile variant with MFMA operands prefetched into registers; the sums of
+// conv_dma's single-group tiles, bit for bit, or with p.slice_major those of
+// conv_halo.  conv_pipe_ok: Cp % 64 == 0, at
+// most 32 taps, no split-K.
+bool conv_pipe_ok(const ConvParams& p);
+bool conv_pipe_tile_supported(int bm, int bn, int stages, int threads);
+hipError_t launch_conv_pipe(const ConvParams& p, int bm, int bn, int stages, int threads, hipStream_t s);
 // 3x3 stride-1 pad-1 convolution that stages each 64-channel slice of the
 // input window of a tile (its output pixels' rows plus a one-pixel halo) in
 // LDS once and forms all nine taps from it; weights stream per tap through

@@ -110,6 +110,7 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_pipe_kernel(ConvParams p) {
   // Reduction position of the next stage to fill and its operand offsets;
   // fill<q> issues load q of that stage (all activation rows, then the weight
   // rows), advance() moves to the next one.
+  const bool slice_major = p.slice_major != 0;
   int r = 0, s = 0, c = 0, issued = 0;
   auto fill = [&](int slot, auto q_tag) {
     constexpr int q = decltype(q_tag)::value;
@@ -128,24 +129,17 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_pipe_kernel(ConvParams p) {
   };
   auto advance = [&] {
     ++issued;
-    if (p.slice_major) {
-      if (++s == p.S) {
-        s = 0;
-        if (++r == p.R) {
-          r = 0;
-          c += kBK;
-        }
-      }
-      return;
-    }
-    c += kBK;
-    if (c == p.Cp) {
-      c = 0;
-      if (++s == p.S) {
-        s = 0;
-        ++r;
-      }
-    }
+    // (one straight line of selects: with a branch here the compiler keeps the
+    // position in scratch memory, which doubles the kernel's time)
+    const int c1 = c + kBK;
+    const bool step = slice_major || c1 == p.Cp;  // to the next tap
+    const int s1 = step ? s + 1 : s;
+    const bool wrap_s = s1 == p.S;
+    const int r1 = wrap_s ? r + 1 : r;
+    const bool wrap_r = slice_major && r1 == p.R;
+    s = wrap_s ? 0 : s1;
+    r = wrap_r ? 0 : r1;
+    c = slice_major ? (wrap_r ? c1 : c) : (step ? 0 : c1);
   };
 
   f32x4 acc[TN][TM];

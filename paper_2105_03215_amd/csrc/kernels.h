@@ -266,6 +266,14 @@ hipError_t launch_add_bf16(const bf16_t* a, const bf16_t* b, bf16_t* y, int64_t 
 hipError_t launch_add_f32(const float* a, const float* b, float* y, int64_t n, int act, float alpha,
                           hipStream_t s);
 
+// Tiled boundary transforms of 4-D tensors (layout.hip): x to y, NCHW (bf16 or
+// f32) to NHWC bf16 / codes (to_nhwc) or back; codes are quantized with
+// scale = fl32(1 / S), dequantized with scale = fl32(S).  For shapes that
+// layout_tiled accepts; the launchers below take them there.
+bool layout_tiled(int64_t N, int C, int64_t HW, int Cp, bool codes);
+hipError_t launch_layout(const void* x, void* y, bool to_nhwc, bool bf16, bool codes, int N, int C, int HW, int Cp,
+                         float scale, int zp, hipStream_t s);
+
 // Boundary transforms.  src_bf16 / dst_bf16 select the external dtype.
 hipError_t launch_nchw_to_nhwc(const void* x, bool src_bf16, bf16_t* y, int N, int C, int H,
                                int W, int Cp, hipStream_t s);

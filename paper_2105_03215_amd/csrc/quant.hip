@@ -19,6 +19,7 @@ __device__ __forceinline__ float load_f(const void* x, bool bf16, int64_t i) {
   return bf16 ? bf16_to_f32(reinterpret_cast<const bf16_t*>(x)[i]) : reinterpret_cast<const float*>(x)[i];
 }
 
+// (rows of a dense input and the images that layout.hip does not take)
 // One thread per (n, 16-channel group, h, w), w fastest: the 16 reads of a
 // thread are coalesced across the wave along w, the write is 16 bytes.
 __global__ __launch_bounds__(kThreads) void quantize_kernel(const void* x, int src_bf16, int8_t* y, int N, int C,
@@ -264,6 +265,8 @@ __global__ __launch_bounds__(kThreads) void add_i8_kernel(QAddParams p) {
 hipError_t launch_quantize_i8(const void* x, bool src_bf16, int8_t* y, int N, int C, int H, int W, int Cp,
                               float inv_scale, int zp, hipStream_t s) {
   if (Cp % 16 != 0 || Cp < C) return hipErrorInvalidValue;
+  if (layout_tiled(N, C, (int64_t)H * W, Cp, true))
+    return launch_layout(x, y, true, src_bf16, true, N, C, H * W, Cp, inv_scale, zp, s);
   quantize_kernel<<<grid_for((int64_t)N * (Cp / 16) * H * W), kThreads, 0, s>>>(x, src_bf16 ? 1 : 0, y, N, C, H, W,
                                                                                  Cp, inv_scale, zp);
   return hipGetLastError();
@@ -280,6 +283,8 @@ hipError_t launch_quantize_im2col_i8(const void* x, bool src_bf16, int8_t* y, co
 hipError_t launch_dequantize_i8(const int8_t* x, void* y, bool dst_bf16, int N, int C, int H, int W, int Cp,
                                 float scale, int zp, hipStream_t s) {
   if (Cp < C) return hipErrorInvalidValue;
+  if (Cp % 16 == 0 && layout_tiled(N, C, (int64_t)H * W, Cp, true))
+    return launch_layout(x, y, false, dst_bf16, true, N, C, H * W, Cp, scale, zp, s);
   dequantize_kernel<<<grid_for((int64_t)N * C * H * W), kThreads, 0, s>>>(x, y, dst_bf16 ? 1 : 0, N, C, H, W, Cp,
                                                                           scale, zp);
   return hipGetLastError();

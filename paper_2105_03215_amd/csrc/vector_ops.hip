@@ -323,7 +323,8 @@ __global__ __launch_bounds__(kThreads) void add_f32_kernel(const float* a, const
 }
 
 // ---------------------------------------------------------------------------
-// NCHW (f32 or bf16) -> NHWC bf16 with Cp >= C channels (pad zero).  Thread
+// NCHW (f32 or bf16) -> NHWC bf16 with Cp >= C channels (pad zero), for images of
+// at most 8 channels or fewer than 16 pixels (others: layout.hip).  Thread
 // per (n, channel group, h, w) with w fastest: reads are contiguous along w
 // for each channel; each thread writes one 16-byte vector.
 // Grid x over the pixels of an image, y over (image, channel group): every
@@ -581,6 +582,7 @@ hipError_t launch_nchw_to_nhwc(const void* x, bool src_bf16, bf16_t* y, int N, i
                                int W, int Cp, hipStream_t s) {
   const int64_t HW = (int64_t)H * W, G = Cp / 8;
   if (HW == 0 || G == 0 || N == 0) return hipSuccess;
+  if (layout_tiled(N, C, HW, Cp, false)) return launch_layout(x, y, true, src_bf16, false, N, C, (int)HW, Cp, 0.f, 0, s);
   if (HW >= (int64_t(1) << 31) || G > kMaxGridY) return hipErrorInvalidValue;
   const int chunk = (int)std::min<int64_t>(N, kMaxGridY / G);
   const size_t esz = src_bf16 ? 2 : 4;
@@ -601,6 +603,7 @@ hipError_t launch_nhwc_to_nchw(const bf16_t* x, void* y, bool dst_bf16, int N, i
                                int W, int Cp, hipStream_t s) {
   const int64_t HW = (int64_t)H * W, G = Cp / 8;
   if (HW == 0 || G == 0 || N == 0) return hipSuccess;
+  if (layout_tiled(N, C, HW, Cp, false)) return launch_layout(x, y, false, dst_bf16, false, N, C, (int)HW, Cp, 0.f, 0, s);
   if (HW >= (int64_t(1) << 31) || G > kMaxGridY) return hipErrorInvalidValue;
   const int chunk = (int)std::min<int64_t>(N, kMaxGridY / G);
   const size_t esz = dst_bf16 ? 2 : 4;

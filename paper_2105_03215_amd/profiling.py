@@ -186,7 +186,8 @@ KERNEL_CLASSES = {
                 "avgpool_i8_kernel"),
     "add": ("add_bf16_kernel", "add_i8_kernel"),
     "boundary transform": ("nchw_to_nhwc_kernel", "nhwc_to_nchw_kernel", "rows_to_padded_kernel",
-                           "padded_to_rows_kernel", "cast_kernel", "quantize_kernel", "dequantize_kernel",
+                           "padded_to_rows_kernel", "cast_kernel", "quantize_kernel", "dequantize_kernel", "to_nhwc_kernel",
+                           "to_nchw_kernel",
                            "quantize_im2col_kernel"),
     "fp32 conv": ("conv_f32_kernel", "conv_f32_regs_kernel"),
 }

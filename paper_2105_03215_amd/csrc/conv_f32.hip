@@ -1,8 +1,8 @@
-// fp32 convolution for fp32 graphs: direct NCHW evaluation of the conv
-// composite, one thread per output, fused multiply-adds in fp32 over the
+// fp32 convolution on the vector ALU, for what the matrix-core kernel does not
+// take (grouped convs, more than 32 taps, inputs of 2 GiB and more): direct
+// NCHW evaluation of the conv composite, one thread per output, fused multiply-adds in fp32 over the
 // reduction in (c, r, s) order, then bias, residual, activation.  Dense runs
-// as the 1x1 case on [M, K, 1, 1].  These graphs are small (the fp32 path
-// exists for exactness, not throughput); consecutive threads take
+// as the 1x1 case on [M, K, 1, 1]; consecutive threads take
 // consecutive output columns so input rows are read contiguously.
 #include "device_common.h"
 

@@ -32,7 +32,7 @@ constexpr int kKPad = 64;     // packed reduction length is padded to this (the 
 constexpr int kHaloStages = 3;  // halo kernel weight ring: 3 stages of one kernel row (built-in choice)
 
 struct PackJob {
-  enum Kind { ConvW, DwW, DwW32, Vec, Copy, StemW, Host } kind;  // Host: copy blob n, built on the host
+  enum Kind { ConvW, DwW, DwW32, RowsW32, Vec, Copy, StemW, Host } kind;  // Host: copy blob n, built on the host
   int cidx = -1;       // constant index
   int64_t dst = 0;     // byte offset in the weights region
   int K = 0, Cg = 0, R = 0, S = 0, Cp = 0, Kgp = 0, rows = 0;
@@ -1185,6 +1185,29 @@ void Planner::plan_node(int ni) {
       p.sh = n.stride[0], p.sw = n.stride[1], p.pt = n.pad[0], p.pl = n.pad[1];
       p.groups = n.groups, p.act = (int)n.act;
       p.alpha = n.alpha;
+      if (conv_f32_mfma_ok(p)) {  // the matrix-core kernel, its weight rows padded
+        const int crs = Cg * R * S, rows = (int)rup(K, 64);
+        p.ldw = (int)rup(crs, 256);
+        L.w = wslot((int64_t)rows * p.ldw * 4);
+        jobs.push_back({PackJob::RowsW32, wc, L.w.off, K, 0, 0, 0, 0, p.ldw, rows, crs, 0});
+        if (!(H == 1 && W == 1 && R == 1 && S == 1)) {
+          std::vector<uint8_t> b((size_t)p.ldw * sizeof(F32Tap), 0);
+          F32Tap* t = reinterpret_cast<F32Tap*>(b.data());
+          for (int kk = 0; kk < crs; ++kk) {
+            const int c = kk / (R * S), rs = kk - c * R * S;
+            t[kk].off = ((c * H + rs / S) * W + rs % S) * 4;
+            t[kk].bit = 1u << rs;
+          }
+          L.other = host_blob(std::move(b));
+        }
+        if (bc >= 0) {
+          L.bias = wslot(K * 4);
+          jobs.push_back({PackJob::Vec, bc, L.bias.off, 0, 0, 0, 0, 0, 0, 0, K, K});
+        }
+        name(L, "conv_f32_mfma");
+        e->launches.push_back(L);
+        return;
+      }
       L.w = wslot(numel(ws) * 4);
       jobs.push_back({PackJob::Copy, wc, L.w.off, 0, 0, 0, 0, 0, 0, 0, (int)numel(ws), (int)numel(ws)});
       if (bc >= 0) {
@@ -2046,7 +2069,8 @@ hipError_t exec(const Launch& L, const RunCtx& c) {
       p.bias = (const float*)c.ptr(L.bias);
       p.res = (const float*)c.ptr(L.res);
       p.y = (float*)c.ptr(L.y);
-      return launch_conv_f32(p, c.s);
+      p.taps = (const F32Tap*)c.ptr(L.other);
+      return p.ldw > 0 ? launch_conv_f32_mfma(p, c.s) : launch_conv_f32(p, c.s);
     }
     case Launch::Depthwise: {
       DwParams p = L.dw;
@@ -2261,6 +2285,9 @@ Status build_device_state(Engine* e, Planner& pl, const byoc_const* consts) {
           break;
         case PackJob::DwW32:
           err = launch_pack_dw_weights_f32(src, sb, (float*)dst, j.K, j.R, j.S, j.Cp, nullptr);
+          break;
+        case PackJob::RowsW32:
+          err = launch_pack_rows_f32(src, sb, (float*)dst, j.K, j.n, j.Kgp, j.rows, nullptr);
           break;
         case PackJob::Vec:
           err = launch_pack_vector_f32(src, sb, (float*)dst, j.n, j.n_out, nullptr);

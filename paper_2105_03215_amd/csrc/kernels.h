@@ -218,16 +218,31 @@ hipError_t launch_splitk_reduce(const ConvParams& p, hipStream_t s);
 
 // fp32 direct convolution over NCHW with generic groups (1 or depthwise);
 // dense is the 1x1 case on [M, K, 1, 1].
+// One reduction element kk = (c*R + r)*S + s of the matrix-core fp32 conv: byte
+// offset of its input from a pixel's window origin and the bit of tap (r, s)
+// (none past the end).
+struct F32Tap {
+  int32_t off;
+  uint32_t bit;
+};
 struct ConvF32Params {
   const float* x;
-  const float* w;  // OIHW [K][C/groups][R][S]
+  const float* w;  // OIHW [K][C/groups][R][S]; matrix-core kernel: the same rows padded to [rup(K, 64)][ldw] with zeros
   const float* bias;
   const float* res;  // NCHW like y, or nullptr
   float* y;
   int N, C, H, W, K, P, Q, R, S, sh, sw, pt, pl, groups, act;
   float alpha;  // leaky ReLU slope
+  int ldw;      // > 0: weight row stride (multiple of 256 floats), the matrix-core kernel
+  const F32Tap* taps;    // [ldw] (images; not read for a dense layer)
+  bool vec4, vec4_out;   // (set by its launcher: aligned 16-byte accesses of a dense layer)
 };
 hipError_t launch_conv_f32(const ConvF32Params& p, hipStream_t s);
+// groups == 1, at most 32 taps, sizes within the index math: conv and dense on the fp32 matrix cores
+bool conv_f32_mfma_ok(const ConvF32Params& p);
+hipError_t launch_conv_f32_mfma(const ConvF32Params& p, hipStream_t s);
+hipError_t launch_pack_rows_f32(const void* src, bool src_bf16, float* dst, int K, int n, int ld, int rows,
+                                hipStream_t s);
 
 // Depthwise conv NHWC bf16: weights packed [R*S][Cp] bf16, bias fp32 [Cp].
 struct DwParams {

@@ -189,7 +189,7 @@ KERNEL_CLASSES = {
                            "padded_to_rows_kernel", "cast_kernel", "quantize_kernel", "dequantize_kernel", "to_nhwc_kernel",
                            "to_nchw_kernel",
                            "quantize_im2col_kernel"),
-    "fp32 conv": ("conv_f32_kernel", "conv_f32_regs_kernel"),
+    "fp32 conv": ("conv_f32_kernel", "conv_f32_regs_kernel", "conv_f32_mfma_kernel"),
 }
 
 

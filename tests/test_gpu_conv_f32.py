@@ -1,0 +1,62 @@
+"""fp32 convs and dense layers on the matrix cores: each tile of the launch rule
+at sizes that do not fill it - pixels, channels and reductions around the
+tile edges, strides, padding, buffers aligned to one element - against the exact
+oracle.  Bound per element: (terms + 3) rounding errors of 2^-24, each at most the
+summed magnitudes of the terms."""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2105_03215_amd import capi, runtime
+from paper_2105_03215_amd.workloads import GraphBuilder
+from parity_util import announce, term_scale_graph
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+# n, c, h, w, k, (r, s), stride, pad, act, residual
+CONVS = [(1, 1, 3, 3, 1, (1, 1), 1, 0, None, False), (1, 16, 7, 9, 17, (3, 3), 1, 1, "relu", False),
+         (2, 27, 13, 11, 33, (5, 5), 2, 2, "relu6", False), (1, 64, 28, 28, 64, (3, 3), 1, 1, "relu", True),
+         (4, 37, 30, 31, 70, (3, 3), 1, 1, "leaky", False), (6, 20, 56, 55, 40, (3, 3), 1, 1, "relu", False),
+         (3, 5, 40, 41, 130, (1, 7), 1, 3, "gelu", False), (5, 129, 33, 17, 66, (1, 1), 2, 0, None, False),
+         (2, 6, 20, 20, 24, (4, 8), 1, 2, None, False), (1, 3, 24, 24, 16, (7, 7), 2, 3, "relu", False)]
+# rows, in, out, act, residual
+DENSE = [(1, 30, 7, None, False), (3, 768, 300, "gelu", False), (30, 257, 64, "relu", True), (257, 64, 514, None, False),
+         (700, 100, 600, "relu6", True), (2500, 36, 1000, "leaky", False)]
+
+
+def _check(wl, terms, what):
+    announce("fp32 " + what)
+    ref = oracle.run_graph(wl.graph, wl.consts, wl.inputs, mode="exact")[0]
+    scale = term_scale_graph(wl.graph, wl.consts, wl.inputs)[0]
+    with capi.Subgraph(wl.graph, wl.consts, device=0) as sg:
+        for offset in (0, 1):  # elements past an allocation's alignment
+            bufs = []
+            for a in wl.inputs + [np.full(ref.shape, np.nan, dtype=np.float32)]:
+                t = torch.empty(a.size + offset, dtype=torch.float32, device=DEV)[offset:].view(a.shape)
+                bufs.append(t.copy_(torch.from_numpy(np.ascontiguousarray(a))))
+            sg.run(bufs[:-1], bufs[-1:])
+            torch.cuda.synchronize()
+            err = np.abs(runtime.to_host_f64(bufs[-1]) - ref)
+            assert (err <= (terms + 3) * 2.0 ** -24 * np.abs(scale) + 1e-30).all(), (what, offset, float(err.max()))
+
+
+@pytest.mark.parametrize("case", CONVS, ids=["x".join(map(str, c[:5])) for c in CONVS])
+def test_conv(case):
+    n, c, h, w, k, r, stride, pad, act, res = case
+    g = GraphBuilder("f32_mfma", 5000 + CONVS.index(case), dtype="f32")
+    x = g.input("x", [n, c, h, w], "normal")
+    g.output(g.conv(x, k, r, stride=stride, pad=pad, act=act, residual=x if res else None, name="y"))
+    _check(g.finish(), c * r[0] * r[1], "conv %s" % (case,))
+
+
+@pytest.mark.parametrize("case", DENSE, ids=["x".join(map(str, c[:3])) for c in DENSE])
+def test_dense(case):
+    m, kin, n, act, res = case
+    g = GraphBuilder("f32_mfma_dense", 5100 + DENSE.index(case), dtype="f32")
+    x = g.input("x", [m, kin], "normal")
+    r = g.input("r", [m, n], "normal") if res else None
+    g.output(g.dense(x, n, act=act, residual=r, w_std=0.05, name="y"))
+    _check(g.finish(), kin, "dense %s" % (case,))

@@ -32,20 +32,37 @@
 // and instruction, and no barrier after the loop.  LDS weight rows use the
 // swizzle key (row & 3) | (row & 8) / 2, which keeps those row sets free
 // of bank conflicts (8 consecutive lanes hold 8 different keys).
+//
+// int8 codes (I8): a 128-byte row holds 128 channels, the same two k-steps of
+// v_mfma_i32_16x16x64_i8 per stage, exact int32 sums, and the int8 kernels'
+// epilogue (8-byte stores; not on the 256x256 tile, where it spills).  6272 x
+// 1024 x 256 with a residual, with events: 16.1 us on conv_i8's 128x64 tile, 11.9 on
+// 128x128 here.
 #include <type_traits>
 
 #include "lds_dma.h"
+#include "quant_epilogue.h"
 
 namespace byoc {
 namespace {
 
 using namespace dma;
 
-constexpr int kBK = 64;       // reduction elements per stage
-constexpr int kCH = kBK / 8;  // 16-byte chunks per LDS row
+constexpr int kCH = 8;  // 16-byte chunks per LDS row
 
-template <int BM, int BN, int WM, int WN, int NS>
-__global__ __launch_bounds__(64 * WM * WN) void conv_pipe_kernel(ConvParams p) {
+__device__ __forceinline__ f32x4 mma(uint4 a, uint4 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a), as_bf16x8(b), c, 0, 0, 0);
+}
+__device__ __forceinline__ i32x4 mma(uint4 a, uint4 b, i32x4 c) {
+  return __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4, a), __builtin_bit_cast(i32x4, b), c, 0, 0, 0);
+}
+
+template <int BM, int BN, int WM, int WN, int NS, bool I8>
+__global__ __launch_bounds__(64 * WM * WN) void conv_pipe_kernel(QConvParams q) {
+  const ConvParams& p = q.g;
+  constexpr int ES = I8 ? 1 : 2;     // bytes per element
+  constexpr int kBK = 128 / ES;      // reduction elements per stage
+  using Acc = std::conditional_t<I8, i32x4, f32x4>;
   constexpr int kNT = 64 * WM * WN;
   constexpr int kRowsPerPass = kNT / kCH;  // rows one load instruction of every wave covers
   constexpr int WTM = BM / WM, WTN = BN / WN;
@@ -72,7 +89,7 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_pipe_kernel(ConvParams p) {
   if (!place_tile<BM, BN>(p, &tm, &tn)) return;
   const int m0 = tm * BM;
   const int n0 = tn * BN;
-  const int nst = p.Kg / kBK;  // (Cp % 64 == 0)
+  const int nst = p.Kg / kBK;  // (Cp is a multiple of it)
 
   // Activation rows of this thread: element offset of the row's window origin
   // plus its chunk; tapmask bit r*S+s set when that tap lies inside the image.
@@ -90,7 +107,7 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_pipe_kernel(ConvParams p) {
       const int pp = mdiv(pq, p.mg_q);
       const int ih0 = pp * p.sh - p.pt;
       const int iw0 = (pq - pp * p.Q) * p.sw - p.pl;
-      off = ((n * p.H + ih0) * p.W + iw0) * p.Cp + cva * 8;
+      off = ((n * p.H + ih0) * p.W + iw0) * p.Cp + cva * (16 / ES);
       const int r_lo = max(0, -ih0), r_hi = min(p.R, p.H - ih0);
       const int s_lo = max(0, -iw0), s_hi = min(p.S, p.W - iw0);
       const uint32_t cols = s_hi > s_lo ? (uint32_t)(((1ull << s_hi) - 1ull) & ~((1ull << s_lo) - 1ull)) : 0u;
@@ -105,7 +122,7 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_pipe_kernel(ConvParams p) {
   // (packed rows are padded to 256, every tile's channels among them or read as zeros past the buffer)
   uint32_t wvoff[BR];
 #pragma unroll
-  for (int i = 0; i < BR; ++i) wvoff[i] = (uint32_t)(((n0 + r0 + i * kRowsPerPass) * p.Kgp + cvb * 8) * 2);
+  for (int i = 0; i < BR; ++i) wvoff[i] = (uint32_t)((n0 + r0 + i * kRowsPerPass) * p.Kgp * ES + cvb * 16);
 
   // Reduction position of the next stage to fill and its operand offsets;
   // fill<q> issues load q of that stage (all activation rows, then the weight
@@ -113,18 +130,18 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_pipe_kernel(ConvParams p) {
   const bool slice_major = p.slice_major != 0;
   int r = 0, s = 0, c = 0, issued = 0;
   auto fill = [&](int slot, auto q_tag) {
-    constexpr int q = decltype(q_tag)::value;
+    constexpr int q = decltype(q_tag)::value;  // (load number)
     uint4* dst = ring + slot * STAGE;
     const bool live = issued < nst;
     if constexpr (q < AR) {
       const int tap = (r * p.W + s) * p.Cp + c;
       const int bit = (r * p.S + s) & 31;
-      const uint32_t off = live && ((tapmask[q] >> bit) & 1u) ? (uint32_t)(pix[q] + tap) * 2u : kOOB;
+      const uint32_t off = live && ((tapmask[q] >> bit) & 1u) ? (uint32_t)(pix[q] + tap) * ES : kOOB;
       lds_fill16(xr, __builtin_amdgcn_readfirstlane(lds_addr(dst + (q * kRowsPerPass + wave * 8) * kCH)), off);
     } else {
       constexpr int i = q - AR;
       lds_fill16(wr, __builtin_amdgcn_readfirstlane(lds_addr(dst + (BM + i * kRowsPerPass + wave * 8) * kCH)),
-                 live ? wvoff[i] + (uint32_t)((r * p.S + s) * p.Cp + c) * 2u : kOOB);
+                 live ? wvoff[i] + (uint32_t)((r * p.S + s) * p.Cp + c) * ES : kOOB);
     }
   };
   auto advance = [&] {
@@ -142,11 +159,11 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_pipe_kernel(ConvParams p) {
     c = slice_major ? (wrap_r ? c1 : c) : (step ? 0 : c1);
   };
 
-  f32x4 acc[TN][TM];
+  Acc acc[TN][TM];
 #pragma unroll
   for (int i = 0; i < TN; ++i)
 #pragma unroll
-    for (int j = 0; j < TM; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < TM; ++j) acc[i][j] = Acc{0, 0, 0, 0};
 
   // LDS offsets (uint4) of this lane's operand rows at chunk 0 of k-step 0;
   // the slot of chunk ks * 4 + lane / 16 is that XOR the row's key
@@ -159,16 +176,16 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_pipe_kernel(ConvParams p) {
     brow[ks] = (BM + wn * WTN + 8 * (lr >> 2) + (lr & 3)) * kCH + ((ks * 4 + lc) ^ ((lr & 3) | (lr & 4)));
   }
   struct Frags {
-    bf16x8 a[TN], b[TM];
+    uint4 a[TN], b[TM];
   };
   constexpr int NR = TN + TM;  // operand reads per k-step
   auto read1 = [&](Frags& f, int slot, auto ks_tag, auto q_tag) {
     constexpr int ks = decltype(ks_tag)::value, q = decltype(q_tag)::value;
     const uint4* st = ring + slot * STAGE;
     if constexpr (q < TN)
-      f.a[q] = as_bf16x8(st[brow[ks] + ((q >> 1) * 32 + (q & 1) * 4) * kCH]);
+      f.a[q] = st[brow[ks] + ((q >> 1) * 32 + (q & 1) * 4) * kCH];
     else
-      f.b[q - TN] = as_bf16x8(st[arow[ks] + (q - TN) * 16 * kCH]);
+      f.b[q - TN] = st[arow[ks] + (q - TN) * 16 * kCH];
   };
   // The MFMAs of one k-step from `cur`, with the operand reads of the next
   // k-step and (FILL) the fills of one stage spread between them: issued in
@@ -181,7 +198,7 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_pipe_kernel(ConvParams p) {
       constexpr int j = decltype(jj)::value;
 #pragma unroll
       for (int i = 0; i < TN; ++i)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur.a[i], cur.b[j], acc[i][j], 0, 0, 0);
+        acc[i][j] = mma(cur.a[i], cur.b[j], acc[i][j]);
       static_for<0, NR>([&](auto q) {
         if constexpr (decltype(q)::value * RG / NR == j) read1(nxt, rslot, ks_tag, q);
       });
@@ -216,6 +233,42 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_pipe_kernel(ConvParams p) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 
   // Epilogue: lane = pixel lr of each pixel tile, channels 32 pr + 8 lc ... + 7
+  if constexpr (I8) {
+    const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<bf16_t*>(p.res), (short)0, p.res ? p.res_bytes : 0, kBufferFlags);
+    const __amdgpu_buffer_rsrc_t br = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<int32_t*>(q.qch), (short)0, ((p.Kp + 255) / 256) * 256 * 8, kBufferFlags);
+#pragma unroll
+    for (int pr = 0; pr < TN / 2; ++pr) {
+      const int k = n0 + wn * WTN + pr * 32 + lc * 8;
+      const bool kok = k < p.Kp;
+      int2 qc[8];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint4 u = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(br, (uint32_t)(k * 8 + e * 16), 0, 0));
+        qc[2 * e] = make_int2((int)u.x, (int)u.y);
+        qc[2 * e + 1] = make_int2((int)u.z, (int)u.w);
+      }
+      uint2 resv[TM];
+#pragma unroll
+      for (int j = 0; j < TM; ++j) {
+        const int m = m0 + wm * WTM + j * 16 + lr;
+        resv[j] = p.res ? __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(
+                              rr, kok && m < p.M ? (uint32_t)(m * p.ldr + k) : kOOB, 0, 0))
+                        : make_uint2(0u, 0u);
+      }
+#pragma unroll
+      for (int j = 0; j < TM; ++j) {
+        const int m = m0 + wm * WTM + j * 16 + lr;
+        if (!kok || m >= p.M) continue;
+        int a[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) a[e] = acc[2 * pr + (e >> 2)][j][e & 3];
+        *(uint2*)(reinterpret_cast<int8_t*>(p.y) + (size_t)m * p.ldy + k) = finish8_i8(a, qc, resv[j], q, m, k);
+      }
+    }
+    return;
+  } else {
   const ActClamp ac = act_clamp_of(p.act, p.alpha);
   const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<bf16_t*>(p.res), (short)0, p.res ? p.res_bytes : 0, kBufferFlags);
@@ -263,16 +316,18 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_pipe_kernel(ConvParams p) {
     epilogue(std::integral_constant<int, 0>{});
   else
     epilogue(std::integral_constant<int, 2>{});
+  }
 }
 
-template <int BM, int BN, int WM, int WN, int NS>
-hipError_t launch_one(const ConvParams& p_in, hipStream_t s) {
+template <int BM, int BN, int WM, int WN, int NS, bool I8>
+hipError_t launch_one(const QConvParams& q_in, hipStream_t s) {
   static_assert(NS * (BM + BN) * 128 <= kLdsLimit, "LDS");
-  ConvParams p = p_in;
-  const int blocks = placed_blocks(p, BM, BN);
-  conv_pipe_kernel<BM, BN, WM, WN, NS><<<blocks, 64 * WM * WN, 0, s>>>(p);
+  QConvParams q = q_in;
+  const int blocks = placed_blocks(q.g, BM, BN);
+  conv_pipe_kernel<BM, BN, WM, WN, NS, I8><<<blocks, 64 * WM * WN, 0, s>>>(q);
   return hipGetLastError();
 }
+
 
 // (bm, bn, waves along bm, waves along bn, ring stages)
 #define BYOC_PIPE_TILES(X) \
@@ -285,9 +340,22 @@ hipError_t launch_one(const ConvParams& p_in, hipStream_t s) {
   X(64, 128, 2, 2, 3)      \
   X(64, 64, 2, 2, 3)
 
+template <bool I8>
+hipError_t launch_any(const QConvParams& q, int bm, int bn, int stages, int threads, hipStream_t s) {
+  if (!conv_pipe_ok(q.g, I8)) return hipErrorInvalidValue;
+#define X(M, N, A, B, S) \
+  if constexpr (!I8 || M * N < 256 * 256)   \
+    if (bm == M && bn == N && stages == S && threads == 64 * A * B) return launch_one<M, N, A, B, S, I8>(q, s);
+  BYOC_PIPE_TILES(X)
+#undef X
+  return hipErrorInvalidValue;
+}
+
 }  // namespace
 
-bool conv_pipe_ok(const ConvParams& p) { return p.Cp % kBK == 0 && p.R * p.S <= 32 && p.splits == 1; }
+bool conv_pipe_ok(const ConvParams& p, bool i8) {
+  return p.Cp % (i8 ? 128 : 64) == 0 && p.R * p.S <= 32 && p.splits <= 1;
+}
 
 bool conv_pipe_tile_supported(int bm, int bn, int stages, int threads) {
 #define X(M, N, A, B, S) \
@@ -298,12 +366,13 @@ bool conv_pipe_tile_supported(int bm, int bn, int stages, int threads) {
 }
 
 hipError_t launch_conv_pipe(const ConvParams& p, int bm, int bn, int stages, int threads, hipStream_t s) {
-  if (!conv_pipe_ok(p)) return hipErrorInvalidValue;
-#define X(M, N, A, B, S) \
-  if (bm == M && bn == N && stages == S && threads == 64 * A * B) return launch_one<M, N, A, B, S>(p, s);
-  BYOC_PIPE_TILES(X)
-#undef X
-  return hipErrorInvalidValue;
+  QConvParams q{};
+  q.g = p;
+  return launch_any<false>(q, bm, bn, stages, threads, s);
+}
+
+hipError_t launch_conv_pipe_i8(const QConvParams& q, int bm, int bn, int stages, int threads, hipStream_t s) {
+  return launch_any<true>(q, bm, bn, stages, threads, s);
 }
 
 }  // namespace byoc

@@ -148,9 +148,10 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // rint(fl32(fl32(a) * m)), ties to even, saturated to +-2^20 (the float32
 // rescaling of int8 graphs; a product followed by a rounding is never
 // contracted).
-__device__ __forceinline__ int rescale(int a, float m) {
-  return (int)__builtin_amdgcn_fmed3f(__builtin_rintf((float)a * m), -1048576.0f, 1048576.0f);
+__device__ __forceinline__ float rescale_f(int a, float m) {
+  return __builtin_amdgcn_fmed3f(__builtin_rintf((float)a * m), -1048576.0f, 1048576.0f);
 }
+__device__ __forceinline__ int rescale(int a, float m) { return (int)rescale_f(a, m); }
 
 // Leaky ReLU on an output code: the offset t = v - zy is kept when t >= 0,
 // otherwise it becomes rint(fl32(t * slope)) (ties to even; |t| < 2^24, so

@@ -125,10 +125,10 @@ constexpr PipeCost kPipeCost[] = {
 // (the windowed 3x3 kernel's 128x64 tile, one workgroup per CU)
 constexpr PipeCost kHaloCost = {128, 64, 512, 3, 1, 3.0, {0.24}, 1.5};
 
-double tile_cost(const PipeCost& c, const ConvParams& p) {
+double tile_cost(const PipeCost& c, const ConvParams& p, int stage = kKPad) {
   constexpr int kCus = 256;
   const int64_t tiles = ((p.M + c.bm - 1) / c.bm) * (int64_t)((p.Kp + c.bn - 1) / c.bn);
-  const int st = (p.Kg + kKPad - 1) / kKPad;
+  const int st = (p.Kg + stage - 1) / stage;
   const double fixed = c.fixed + (p.act == kActGelu ? c.gelu : 0.0);
   const int64_t full = tiles / (kCus * c.occ), rest = tiles % (kCus * c.occ);
   double t = (double)full * (fixed + st * c.stage[c.occ - 1]);
@@ -136,10 +136,14 @@ double tile_cost(const PipeCost& c, const ConvParams& p) {
   return t;
 }
 
-double choose_pipe_tile(const ConvParams& p, ConvTile* t) {
+// (int8 codes: 128 per stage, and no 256x256 tile - its epilogue spills)
+bool pipe_tile_of(const PipeCost& c, bool i8) { return !i8 || c.bm * c.bn < 256 * 256; }
+
+double choose_pipe_tile(const ConvParams& p, bool i8, ConvTile* t) {
   double best = 0.0;
   for (const PipeCost& c : kPipeCost) {
-    const double v = tile_cost(c, p);
+    if (!pipe_tile_of(c, i8)) continue;
+    const double v = tile_cost(c, p, i8 ? 128 : kKPad);
     if (best > 0.0 && v >= best) continue;
     best = v;
     *t = ConvTile{};
@@ -254,6 +258,9 @@ void name_conv_i8(Launch& L) {
   if (L.tile.halo)
     std::snprintf(L.info.name, sizeof(L.info.name), "conv_i8_halo_%dx%d_s%d_lp%d_pb%d", L.tile.bm, L.tile.bn,
                   L.tile.stages, L.tile.lp, L.tile.npb);
+  else if (L.tile.pipe)
+    std::snprintf(L.info.name, sizeof(L.info.name), "conv_i8_pipe_%dx%d_s%d_w%d", L.tile.bm, L.tile.bn, L.tile.stages,
+                  L.tile.threads / 64);
   else
     std::snprintf(L.info.name, sizeof(L.info.name), L.tile.kgroups > 1 ? "conv_i8_%dx%d_s%d_w%d_k%d" : "conv_i8_%dx%d_s%d_w%d",
                   L.tile.bm, L.tile.bn, L.tile.stages, L.tile.threads / 64, L.tile.kgroups);
@@ -1332,7 +1339,7 @@ void Planner::plan_node(int ni) {
       const bool many = builtin && splits == 1 && L.tile.kgroups == 1 && conv_pipe_ok(p) &&
                         ((p.M + 63) / 64) * (int64_t)((Kp + 63) / 64) > 256;
       ConvTile pipe{};
-      const double pipe_cost = many ? choose_pipe_tile(p, &pipe) : 0.0;
+      const double pipe_cost = many ? choose_pipe_tile(p, false, &pipe) : 0.0;
       const int64_t halo_tiles = ((p.M + 127) / 128) * ((Kp + 63) / 64);
       const int64_t halo64_tiles = ((p.M + 63) / 64) * ((Kp + 63) / 64);
       // (wherever the windowed kernel is the 3x3 layer's kernel by its own
@@ -1863,13 +1870,21 @@ void Planner::plan_node_i8(int ni) {
     else if (tiles(128, 64) >= 512) t.bm = 128, t.bn = 64;
     else if (p.M <= 32) t.bm = 32, t.bn = 64;
     else t.bm = 64, t.bn = 64;
+    // more 64x64 tiles than CUs: the cheapest conv_pipe tile (batch 32, ResNet-50:
+    // 256 -> 1024 channels at 14x14 with a residual 16.1 us on 128x64, 11.9 on
+    // conv_pipe's 128x128; 512 -> 2048 at 7x7 11.7 and 10.1)
+    if (conv_pipe_ok(p, true) && tiles(64, 64) > 256) choose_pipe_tile(p, true, &t);
     // BYOC_I8_TILE=<bm>x<bn>s<stages>[w<waves>[k<groups>]] forces a tile (any
     // tile gives the same codes)
     if (const char* te = std::getenv("BYOC_I8_TILE")) {
       int bm = 0, bn = 0, ns = 0, nw = 4, kgr = 1;
       if (std::sscanf(te, "%dx%ds%dw%dk%d", &bm, &bn, &ns, &nw, &kgr) >= 3 &&
           conv_i8_tile_supported(bm, bn, ns, 64 * nw, kgr))
-        t.bm = bm, t.bn = bn, t.stages = ns, t.threads = 64 * nw, t.kgroups = kgr;
+        t.bm = bm, t.bn = bn, t.stages = ns, t.threads = 64 * nw, t.kgroups = kgr, t.pipe = 0;
+      // p<bm>x<bn>s<stages>w<waves>: a conv_pipe tile, where the shape allows
+      if (std::sscanf(te, "p%dx%ds%dw%d", &bm, &bn, &ns, &nw) == 4 && conv_pipe_tile_supported(bm, bn, ns, 64 * nw) &&
+          bm * bn < 256 * 256 && conv_pipe_ok(p, true))
+        t.bm = bm, t.bn = bn, t.stages = ns, t.threads = 64 * nw, t.pipe = 1;
     }
     // 3x3 stride-1 convs with at least 256 input channels and enough 128x64
     // tiles run on the windowed kernel (input window staged in LDS once per
@@ -2130,6 +2145,7 @@ hipError_t exec(const Launch& L, const RunCtx& c) {
       q.qch = (const int32_t*)c.ptr(L.bias);
       q.wtap = (const int32_t*)c.ptr(L.other);
       if (L.tile.halo) return launch_conv_halo_i8(q, L.tile.bm, L.tile.bn, L.tile.stages, L.tile.lp, L.tile.npb, c.s);
+      if (L.tile.pipe) return launch_conv_pipe_i8(q, L.tile.bm, L.tile.bn, L.tile.stages, L.tile.threads, c.s);
       return launch_conv_i8(q, L.tile.bm, L.tile.bn, L.tile.stages, L.tile.threads, L.tile.kgroups, c.s);
     }
     case Launch::MaxPoolI8:
@@ -2596,6 +2612,18 @@ std::vector<ConvTile> conv_i8_candidates(const Launch& L) {
       t.bm = bm, t.bn = 64, t.stages = ns, t.threads = 512, t.halo = 1;
       if (!conv_halo_plan(L.qc.g, bm, 64, ns, &t.lp, &t.npb, true)) continue;
       if (L.tile_default.halo && bm == L.tile_default.bm && ns == L.tile_default.stages) continue;
+      c.push_back(t);
+    }
+  // conv_pipe's tiles
+  if (conv_pipe_ok(L.qc.g, true))
+    for (const PipeCost& k : kPipeCost) {
+      const ConvParams& p = L.qc.g;
+      if (!pipe_tile_of(k, true)) continue;
+      if (((int64_t)(p.M + k.bm - 1) / k.bm) * ((p.Kp + k.bn - 1) / k.bn) < 88 && k.bm * k.bn > 64 * 64) continue;
+      if (p.Kp <= 64 && k.bn > 64) continue;
+      ConvTile t = ConvTile{};
+      t.bm = k.bm, t.bn = k.bn, t.stages = k.stages, t.threads = k.threads, t.pipe = 1;
+      if (L.tile_default.pipe && t.bm == L.tile_default.bm && t.bn == L.tile_default.bn) continue;
       c.push_back(t);
     }
   // single-group tiles of 4 or 8 waves, and 2 or 4 reduction groups of 4

@@ -75,9 +75,9 @@ hipError_t launch_conv_dma(const ConvParams& p, int bm, int bn, int stages, int 
                            hipStream_t s);
 // Large-tile variant with MFMA operands prefetched into registers; the sums of
 // conv_dma's single-group tiles, bit for bit, or with p.slice_major those of
-// conv_halo.  conv_pipe_ok: Cp % 64 == 0, at
-// most 32 taps, no split-K.
-bool conv_pipe_ok(const ConvParams& p);
+// conv_halo.  conv_pipe_ok: Cp % 64 == 0 (int8 codes: 128),
+// at most 32 taps, no split-K.
+bool conv_pipe_ok(const ConvParams& p, bool i8 = false);
 bool conv_pipe_tile_supported(int bm, int bn, int stages, int threads);
 hipError_t launch_conv_pipe(const ConvParams& p, int bm, int bn, int stages, int threads, hipStream_t s);
 // 3x3 stride-1 pad-1 convolution that stages each 64-channel slice of the
@@ -332,6 +332,8 @@ struct QConvParams {
 // 4-wave reduction groups (threads = 256 * kgroups) on 64x64 or 32x64
 // tiles, 2 groups also on 128x64, as far as their rings fit the LDS.
 bool conv_i8_tile_supported(int bm, int bn, int stages, int threads, int kgroups = 1);
+// conv_pipe's tiles on int8 codes; the same codes as launch_conv_i8
+hipError_t launch_conv_pipe_i8(const QConvParams& p, int bm, int bn, int stages, int threads, hipStream_t s);
 hipError_t launch_conv_i8(const QConvParams& p, int bm, int bn, int stages, int threads, int kgroups,
                           hipStream_t s);
 // The windowed 3x3 kernel on codes (conv_halo_plan(..., i8 = true) sizes it):

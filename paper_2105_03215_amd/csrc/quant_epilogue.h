@@ -49,16 +49,36 @@ __device__ __forceinline__ uint2 finish8_i8(int a[8], const int2* qc, uint2 rv, 
     }
   }
   const uint32_t rw[2] = {rv.x, rv.y};
+  auto res_code = [&](int c8) { return (int)(int8_t)(rw[c8 >> 2] >> (8 * (c8 & 3))); };
   uint32_t out[2] = {0u, 0u};
+  auto put = [&](int c8, int v) { out[c8 >> 2] |= ((uint32_t)v & 0xFFu) << (8 * (c8 & 3)); };
+  // The plain and the residual form (one uniform choice for the 8 channels),
+  // in float32: the rescaled terms are integers below 2^21, so their sum and the
+  // clamp relative to zy are exact and one conversion is left.
+  const float lo = (float)(q.lo - q.zy), hi = (float)(q.hi - q.zy);
+  if (!q.leaky && !q.post) {
+    if (!p.res) {
+#pragma unroll
+      for (int c8 = 0; c8 < 8; ++c8)
+        put(c8, q.zy + (int)__builtin_amdgcn_fmed3f(rescale_f(a[c8], __int_as_float(qc[c8].y)), lo, hi));
+    } else {
+#pragma unroll
+      for (int c8 = 0; c8 < 8; ++c8) {
+        const float t = rescale_f(a[c8], __int_as_float(qc[c8].y)) + rescale_f(res_code(c8) - q.zr, q.mr);
+        put(c8, q.zy + (int)__builtin_amdgcn_fmed3f(t, lo, hi));
+      }
+    }
+    return make_uint2(out[0], out[1]);
+  }
 #pragma unroll
   for (int c8 = 0; c8 < 8; ++c8) {
     int v = q.zy + rescale(a[c8], __int_as_float(qc[c8].y));
-    const int rc = (int)(int8_t)(rw[c8 >> 2] >> (8 * (c8 & 3)));
+    const int rc = res_code(c8);
     if (p.res && !q.post) v += rescale(rc - q.zr, q.mr);
     if (q.leaky) v = leaky_code(v, q.zy, q.slope);
     v = min(max(v, q.lo), q.hi);
     if (q.post) v = clip_i8(q.pz + rescale(v - q.zy, q.pm) + rescale(rc - q.zr, q.mr));
-    out[c8 >> 2] |= ((uint32_t)v & 0xFFu) << (8 * (c8 & 3));
+    put(c8, v);
   }
   return make_uint2(out[0], out[1]);
 }

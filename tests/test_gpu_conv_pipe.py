@@ -140,3 +140,34 @@ def test_windowed_kernels_order_is_shared():
     first = outs["built-in", False].view(torch.int16)
     for key, o in outs.items():
         assert torch.equal(o.view(torch.int16), first), key
+
+
+I8_CASES = [
+    # n, c, h, w, k, r, stride, pad, zx, act, residual, output scale
+    (2, 128, 5, 7, 24, 1, 1, 0, 3, None, False, 0.023),
+    (2, 128, 14, 13, 200, 3, 1, 1, 37, "relu", True, 0.023),     # border correction, residual
+    (3, 256, 11, 9, 136, 3, 2, 1, -100, "relu6", False, 0.023),
+    (1, 128, 13, 12, 264, 3, 1, 1, -40, "leaky", True, 0.023),
+    (2, 128, 9, 9, 72, 1, 1, 0, 9, None, True, 1e-6),            # rescaled terms saturate at +-2^20
+    (2, 128, 9, 9, 72, 1, 1, 0, 9, "relu", False, 1e-6),
+]
+
+
+@pytest.mark.parametrize("case", I8_CASES, ids=[str(i) for i in range(len(I8_CASES))])
+def test_int8_tiles_exact(case, monkeypatch):
+    """int8 codes: every conv_pipe tile, the implicit-GEMM kernel and the built-in
+    choice give the oracle's codes."""
+    import numpy as np
+    from oracle import quant as oq
+    from test_gpu_quant import _conv_graph, _run as run_i8
+    g, consts, inputs = _conv_graph(*case[:11], seed=70 + I8_CASES.index(case))
+    g["nodes"][0]["quant"]["scale"] = case[11]
+    ref = oq.run_quantized_graph(g, consts, inputs)[0].astype(np.float64)
+    for tile in [None, "64x64s3w4"] + ["p" + t[1:].replace("t256", "w4").replace("t512", "w8") for t in TILES[1:]]:
+        announce("int8 conv_pipe %s %s" % (case, tile))
+        if tile:
+            monkeypatch.setenv("BYOC_I8_TILE", tile)
+        got, launches = run_i8(g, consts, inputs)
+        name = [l["name"] for l in launches if l["kind"] == "conv_i8"][0]
+        assert not (tile and tile[0] == "p") or name.startswith("conv_i8_pipe_" + tile[1:].split("s")[0]), name
+        assert np.array_equal(got[0], ref), (tile, name)

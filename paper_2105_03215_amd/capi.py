@@ -192,6 +192,12 @@ class Subgraph:
         self.n_in, self.n_out = n_in.value, n_out.value
         self._descs = ([self.io_desc(0, i) for i in range(self.n_in)],
                        [self.io_desc(1, j) for j in range(self.n_out)])
+        # element counts and pointer-array types of a run's buffers, formed once: with
+        # the counts taken per call, checking one input and one output took 12 us of
+        # host time, more than a small subgraph's kernel
+        self._counts = tuple([int(np.prod(d["shape"])) if d["shape"] else 1 for d in ds] for ds in self._descs)
+        self._ptrs = (ctypes.c_void_p * max(self.n_in, 1), ctypes.c_void_p * max(self.n_out, 1))
+        self._torch = None  # (dtypes by desc, device, current raw stream), on the first run
 
     def io_desc(self, is_output, idx):
         d = TensorDesc()
@@ -224,19 +230,36 @@ class Subgraph:
         if len(inputs) != self.n_in or len(outputs) != self.n_out:
             raise ByocError(1, "expected %d inputs and %d outputs, got %d and %d"
                             % (self.n_in, self.n_out, len(inputs), len(outputs)))
-        for what, ts, descs in (("input", inputs, self._descs[0]), ("output", outputs, self._descs[1])):
-            for i, (t, d) in enumerate(zip(ts, descs)):
-                _check_tensor(t, d, self.device, "%s %d" % (what, i))
-        ins = (ctypes.c_void_p * max(len(inputs), 1))(*[_ptr(t) for t in inputs])
-        outs = (ctypes.c_void_p * max(len(outputs), 1))(*[_ptr(t) for t in outputs])
+        io = self._torch
+        for side, ts in enumerate((inputs, outputs)):
+            for i, t in enumerate(ts):
+                if t is None or isinstance(t, int):
+                    continue
+                if io is None:
+                    io = self._torch_io()
+                if not (t.dtype is io[0][side][i] and t.numel() == self._counts[side][i] and t.device == io[1]
+                        and t.is_contiguous()):
+                    _check_tensor(t, self._descs[side][i], self.device, "%s %d" % (("input", "output")[side], i))
+        ins = self._ptrs[0](*[_ptr(t) for t in inputs])
+        outs = self._ptrs[1](*[_ptr(t) for t in outputs])
         if stream is None:
-            import torch
-            s = torch.cuda.current_stream(self.device).cuda_stream
+            s = (io or self._torch_io())[2](self.device)
         elif isinstance(stream, int):
             s = stream
         else:
             s = stream.cuda_stream
         return ins, outs, ctypes.c_void_p(s)
+
+    def _torch_io(self):
+        import torch
+        kinds = {"bf16": torch.bfloat16, "f32": torch.float32}
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is None:
+            def raw(device):
+                return torch.cuda.current_stream(device).cuda_stream
+        self._torch = (tuple([kinds[d["dtype"]] for d in ds] for ds in self._descs),
+                       torch.device("cuda", int(self.device)), raw)
+        return self._torch
 
     def run(self, inputs, outputs, stream=None):
         """Enqueue one run on `stream` (a torch.cuda.Stream, a raw hipStream_t

@@ -34,11 +34,14 @@
 // Weights are the MFMA A operand (16 output channels), pixels the B operand.
 // Every LDS row is 128 bytes (64 bf16 channels) with its 16-byte chunks
 // permuted by the row index (slot = chunk ^ (row & 7)).  The weights of the
-// next slice stream in while the current one computes: the expand and
-// depthwise weights after phase A, the project weights after phase C, each
-// into its own buffer (the depthwise slice double-buffered); every thread
-// issues the same loads (out-of-range ones fill a junk block), so the wait
-// counts are compile-time constants.
+// next slice stream in while the current one computes (the depthwise and
+// project slices double-buffered, where they fit); every thread issues the same loads
+// (out-of-range ones fill a junk block).
+//
+// Latency per slice bounds it - barriers, and phases of a few hundred cycles
+// between them: with two barriers per slice and a small window's expand spread
+// over more waves, the 64-channel block at 14x14 (batch 16, 4x4 tiles) takes 10.8 us;
+// with four barriers and one wave per pixel tile it took 12.9.
 #include <cstdio>
 
 #include "lds_dma.h"
@@ -61,7 +64,13 @@ struct Ir {
   static constexpr int HPX = IH * IW, HPXP = (HPX + 15) / 16 * 16;
   static constexpr int OPX = TH * TW, OPXP = (OPX + 15) / 16 * 16;
   static constexpr int NTA = HPXP / 16, NTB = OPXP / 16;  // 16-pixel tiles
-  static constexpr int TA = (NTA + NW - 1) / NW;          // phase A pixel tiles per wave
+  // phase A: CS groups of waves share the slice's 4 channel tiles where the
+  // window has fewer pixel tiles than waves (a 6x6 window, 3 tiles: 6 waves at
+  // work instead of 3)
+  static constexpr int CS = NTA <= 2 ? 4 : NTA <= 4 ? 2 : 1;
+  static constexpr int CA = 4 / CS;                       // channel tiles per wave
+  static constexpr int NWA = NW / CS;                     // waves along the pixel tiles
+  static constexpr int TA = (NTA + NWA - 1) / NWA;        // pixel tiles per wave
   static constexpr int V = V_;                            // phase B: output rows per thread
   static constexpr int NSTRIP = TH / V * TW;              //   strips of V rows of one column
   // phase B: channels per thread (8, 4 or 2), so that the strips x channel
@@ -84,7 +93,9 @@ struct Ir {
   // 1 KB blocks of float32 biases: [be (FB),] bd (FB), bp (PB)
   static constexpr int FB = FMAX * 4 / 1024, PB = (CT * 16 * 4 + 1023) / 1024;
   static constexpr int BBLK = (EXP ? FB : 0) + FB + PB, LBB = (BBLK + NW - 1) / NW;
-  static constexpr int OFF_B = OFF_WP + WPB;
+  // project slices in flight: two buffers where they fit
+  static constexpr int NWP = OFF_WP + 2 * WPB + (BBLK + 1) * 1024 <= kLdsLimit ? 2 : 1;
+  static constexpr int OFF_B = OFF_WP + NWP * WPB;
   static constexpr int OFF_JUNK = OFF_B + BBLK * 1024;
   static constexpr int MINW = MINW_;  // waves per SIMD the registers are held to
   static constexpr int LDS = OFF_JUNK + 1024;
@@ -95,7 +106,6 @@ struct Ir {
   static constexpr int WPBLK = CT * 2, LWP = (WPBLK + NW - 1) / NW;
   static_assert(CT * 16 <= 320 && FMAX % 256 == 0 && LDS <= kLdsLimit && TH % V == 0 && (V == 1 || S == 1),
                 "shape");
-  static_assert(LWE + LWD <= 63 && LWP <= 63, "vmcnt immediate");
 };
 
 __device__ __forceinline__ uint32_t slot_off(int row, int chunk) {
@@ -235,7 +245,7 @@ __global__ __launch_bounds__(B::NT, B::MINW) void ir_block_kernel(IrParams p) {
       const int row = 8 * blk + (lane >> 3);
       const int c = lk ^ (row & 7);
       const uint32_t off = f < FS && blk < B::WPBLK ? (uint32_t)((row * p.ldP + f * 64 + c * 8) * 2) : kOOB;
-      lds_fill16(wpr, dst(base + B::OFF_WP, blk, B::WPBLK), off);
+      lds_fill16(wpr, dst(base + B::OFF_WP + f % B::NWP * B::WPB, blk, B::WPBLK), off);
     }
   };
 
@@ -267,30 +277,31 @@ __global__ __launch_bounds__(B::NT, B::MINW) void ir_block_kernel(IrParams p) {
 #pragma unroll
   for (int u = 0; u < B::TC; ++u) accC[u] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  for (int f = 0; f < FS; ++f) {
-    // ---- phase A: the slice of the expanded tensor over the window -----------
+  // ---- phase A: slice f of the expanded tensor over the window ---------------
+  auto phase_a = [&](int f) {
     if constexpr (B::EXP) {
-      f32x4 accA[B::TA][4];
+      const int wa = wave % B::NWA, i0 = wave / B::NWA * B::CA;  // pixel tile lane, first channel tile
+      f32x4 accA[B::TA][B::CA];
 #pragma unroll
       for (int t = 0; t < B::TA; ++t)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) accA[t][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < B::CA; ++i) accA[t][i] = f32x4{0.f, 0.f, 0.f, 0.f};
       const char* we = lds + B::OFF_WE;
       const char* xs = lds + B::OFF_X;
       for (int ks = 0; ks < ka; ++ks) {
         const int sl = ks >> 1, c = (ks & 1) * 4 + lq;  // input slice, chunk in it
         const char* wes = we + sl * 64 * B::ROW;
         const char* xss = xs + sl * B::HPXP * B::ROW;
-        uint4 a[4];
+        uint4 a[B::CA];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) a[i] = *(const uint4*)(wes + slot_off(16 * i + l16, c));
+        for (int i = 0; i < B::CA; ++i) a[i] = *(const uint4*)(wes + slot_off(16 * (i0 + i) + l16, c));
 #pragma unroll
         for (int t = 0; t < B::TA; ++t) {
-          const int j = wave + NW * t;
+          const int j = wa + B::NWA * t;
           if (j < B::NTA) {
             const bf16x8 b = as_bf16x8(*(const uint4*)(xss + slot_off(16 * j + l16, c)));
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < B::CA; ++i)
               accA[t][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a[i]), b, accA[t][i], 0, 0, 0);
           }
         }
@@ -298,29 +309,37 @@ __global__ __launch_bounds__(B::NT, B::MINW) void ir_block_kernel(IrParams p) {
       char* es = lds + B::OFF_E;
 #pragma unroll
       for (int t = 0; t < B::TA; ++t) {
-        const int j = wave + NW * t;
+        const int j = wa + B::NWA * t;
         if (j >= B::NTA) continue;
         const int px = 16 * j + l16;
         const int ih = ih0 + px / IW, iw = iw0 + px % IW;
         const bool inside = px < B::HPX && (unsigned)ih < (unsigned)H && (unsigned)iw < (unsigned)W;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float4 bb = *(const float4*)(sbe + f * 64 + 16 * i + 4 * lq);
+        for (int i = 0; i < B::CA; ++i) {
+          const float4 bb = *(const float4*)(sbe + f * 64 + 16 * (i0 + i) + 4 * lq);
           const f32x4 v = accA[t][i];
           // (+ 0: the unfused epilogue adds its zero residual, which turns a -0 into +0)
           float f0 = act_apply<2>((v[0] + bb.x) + 0.f, ace), f1 = act_apply<2>((v[1] + bb.y) + 0.f, ace);
           float f2 = act_apply<2>((v[2] + bb.z) + 0.f, ace), f3 = act_apply<2>((v[3] + bb.w) + 0.f, ace);
           if (!inside) f0 = f1 = f2 = f3 = 0.f;  // the depthwise padding
-          *(uint2*)(es + slot_off(px, 2 * i + (lq >> 1)) + (lq & 1) * 8) =
+          *(uint2*)(es + slot_off(px, 2 * (i0 + i) + (lq >> 1)) + (lq & 1) * 8) =
               make_uint2(pack2_bf16(f0, f1), pack2_bf16(f2, f3));
         }
       }
-      // the slice is in LDS, the expand weights are free
-      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     }
-    issue_we(f + 1);
-    issue_wd(f + 1);
+  };
 
+  // Two barriers per slice: the project step of a slice and the expand of the next
+  // share the stretch between them (they touch different buffers), the depthwise
+  // taps have the other.  Weights of slice f + 2 are issued when both are done
+  // with those they replace, and have a phase B, a barrier's wait and the
+  // next project step to arrive.
+  phase_a(0);
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  issue_we(1);
+  issue_wd(1);
+  if constexpr (B::NWP == 2) issue_wp(1);
+  for (int f = 0; f < FS; ++f) {
     // ---- phase B: depthwise taps of the slice --------------------------------
     // A thread keeps CPT channels (a fixed group: NT is a multiple of the
     // group count) - their taps are float32 in LDS - and finishes a vertical
@@ -373,13 +392,12 @@ __global__ __launch_bounds__(B::NT, B::MINW) void ir_block_kernel(IrParams p) {
         }
       }
     }
-    // the depthwise slice is in LDS; this slice's project weights have landed
-    // (the next expand and depthwise weights, issued after them, may not)
-    wait_barrier<B::LWE + B::LWD>();
+    // the depthwise slice is in LDS, and the weights of slice f + 1
+    wait_barrier<0>();
 
     // ---- phase C: the slice's step of the project reduction -------------------
     {
-      const char* wp = lds + B::OFF_WP;
+      const char* wp = lds + B::OFF_WP + f % B::NWP * B::WPB;
       const char* ds = lds + B::OFF_D;
 #pragma unroll
       for (int u = 0; u < B::TC; ++u) {
@@ -395,11 +413,14 @@ __global__ __launch_bounds__(B::NT, B::MINW) void ir_block_kernel(IrParams p) {
         }
       }
     }
-    // every wave is done with the project weights and the depthwise slice
+    if (f + 1 == FS) break;
+    phase_a(f + 1);
+    // every wave is done with slice f's depthwise slice and project weights and
+    // with slice f + 1's expand weights; slice f + 1 of the expanded tensor is in LDS
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    issue_wp(f + 1);
-    // the next expand and depthwise weights have landed
-    wait_barrier<B::LWP>();
+    issue_we(f + 2);
+    issue_wd(f + 2);
+    issue_wp(f + B::NWP);
   }
 
   // ---- epilogue: bias, the block input, bf16 --------------------------------

@@ -74,6 +74,8 @@ void choose_conv_tile(int64_t M, int Kp, int Kg, ConvTile* t, int* splits, int* 
   if (tiles < 64 && nk >= 8) {
     int s = (int)std::min<int64_t>(nk / 4, (128 + tiles - 1) / tiles);
     s = std::max(1, std::min(s, 16));
+    // For the layers conv_few does not take (channels that are not whole
+    // 64-channel slices, or a reduction so long that its modelled time loses).
     // Measured on MI355X (ResNet-18 block and ResNet-50 at batch 1): where
     // split-K would split only two ways, four reduction groups of 4 waves
     // sharing each tile's stages inside one workgroup (sums added in the
@@ -156,6 +158,42 @@ double choose_pipe_tile(const ConvParams& p, bool i8, ConvTile* t) {
   return best;
 }
 
+void set_few_tile(ConvTile* t, int bm, int bn) {
+  *t = ConvTile{};
+  t->bm = bm;
+  t->bn = bn;
+  t->kgroups = 4;  // (the four waves are its reduction groups)
+  t->few = 1;
+}
+
+// conv_few's tile and modelled time (us) for a layer: the largest tile that
+// still makes 180 workgroups, else the smallest; a launch with its prologue and epilogue
+// costs about 4 us and a CU takes in operands at 26 us per MB.  Measured on MI355X,
+// us per layer (modelled): 64 -> 64 3x3 at 56x56 5.5 (5.9), 128 -> 128 at 28x28
+// 6.1 (6.8), 256 -> 256 at 14x14 7.1 (7.8), batch 4 11.5 (11.5), 512 -> 512 at 7x7
+// 11.3 (11.5), batch 8 19.0 (19.0).
+double choose_few_tile(const ConvParams& p, ConvTile* t) {
+  auto groups = [&](int bm, int bn) { return ((p.M + bm - 1) / bm) * (int64_t)((p.Kp + bn - 1) / bn); };
+  int bm = 16, bn = 16;
+  if (groups(32, 32) >= 180) bm = bn = 32;
+  else if (groups(16, 32) >= 180) bn = 32;
+  set_few_tile(t, bm, bn);
+  const double mb = (double)((groups(bm, bn) + 255) / 256) * (bm + bn) * p.Kg * 2.0 / (1 << 20);
+  return 4.0 + 26.0 * mb;
+}
+
+// The time of what choose_conv_tile chose for a layer of few 64x64 tiles, measured
+// the same way: split-K with its reduce launch 8 us + 0.34 per stage of a
+// split (256 -> 256 at 14x14 9.9, modelled 9.7; batch 4 12.4, 12.1; 512 -> 512 at 7x7
+// 10.3, 9.7), four reduction groups 6.6 + 0.34 per stage of a group (64 -> 64
+// at 56x56 7.6, 7.6), one 64x64 tile per workgroup 5.5 + 0.25 per stage.
+double few_tiles_cost(const ConvTile& t, int splits, int kps, int Kg) {
+  const int nk = (Kg + kKPad - 1) / kKPad;
+  if (splits > 1) return 8.0 + 0.34 * kps;
+  if (t.kgroups > 1) return 6.6 + 0.34 * ((nk + t.kgroups - 1) / t.kgroups);
+  return 5.5 + 0.25 * nk;
+}
+
 // Tuning override (environment, read at engine creation):
 // BYOC_CONV_TILE=<bm>x<bn>[x<mfma 16|32>] (register-staged) or d<bm>x<bn>s<stages>
 // (HBM->LDS pipeline) forces a compiled tile, BYOC_CONV_SPLIT=<n> a
@@ -181,6 +219,12 @@ void apply_tile_override(int Kg, ConvTile* t, int* splits, int* kps) {
         t->threads = 512;
         t->kgroups = 1;
         t->halo = 2;  // requested; resolved against the shape by the planner
+      }
+    } else if (e[0] == 'f') {
+      // f<bm>x<bn>: conv_few kernel (convs it takes; others keep their tile)
+      if (std::sscanf(e + 1, "%dx%d", &bm, &bn) == 2 && (bm == 16 || bm == 32) && (bn == 16 || bn == 32)) {
+        set_few_tile(t, bm, bn);
+        t->few = 2;  // requested; resolved against the shape by the planner
       }
     } else if (e[0] == 'p') {
       // p<bm>x<bn>s<stages>t<threads>: conv_pipe kernel (convs it takes; others keep their tile)
@@ -270,6 +314,9 @@ void name_conv(Launch& L) {
   if (L.tile.halo)
     std::snprintf(L.info.name, sizeof(L.info.name), "conv_halo_%dx%d_s%d_lp%d_pb%d", L.tile.bm, L.tile.bn,
                   L.tile.stages, L.tile.lp, L.tile.npb);
+  else if (L.tile.few)
+    std::snprintf(L.info.name, sizeof(L.info.name), "conv_few_%dx%d_k%d_w%d", L.tile.bm, L.tile.bn, L.tile.kgroups,
+                  L.tile.threads / 64);
   else if (L.tile.pipe)
     std::snprintf(L.info.name, sizeof(L.info.name), "conv_pipe_%dx%d_s%d_w%d", L.tile.bm, L.tile.bn, L.tile.stages,
                   L.tile.threads / 64);
@@ -1307,11 +1354,11 @@ void Planner::plan_node(int ni) {
     int splits, kps;
     choose_conv_tile(p.M, Kp, p.Kg, &L.tile, &splits, &kps);
     apply_tile_override(p.Kg, &L.tile, &splits, &kps);
-    if (L.tile.pipe == 2) {  // a forced conv_pipe tile forgoes split-K
+    if (L.tile.pipe == 2 || L.tile.few == 2) {  // a forced conv_pipe or conv_few tile forgoes split-K
       ConvParams q = p;
       q.splits = 1;
-      if (conv_pipe_ok(q)) {
-        L.tile.pipe = 1;
+      if (L.tile.few ? conv_few_ok(q) : conv_pipe_ok(q)) {
+        (L.tile.few ? L.tile.few : L.tile.pipe) = 1;
         splits = 1;
         kps = (p.Kg + kKPad - 1) / kKPad;
       } else {
@@ -1321,6 +1368,18 @@ void Planner::plan_node(int ni) {
     }
     p.splits = splits;
     p.k_tiles_per_split = kps;
+    const bool builtin = !std::getenv("BYOC_CONV_TILE") && !std::getenv("BYOC_CONV_SPLIT");
+    // few 64x64 tiles: conv_few, where its modelled time is less
+    if (builtin && ((p.M + 63) / 64) * (int64_t)((Kp + 63) / 64) <= 64) {
+      ConvParams q = p;
+      q.splits = 1;
+      ConvTile few{};
+      if (conv_few_ok(q) && choose_few_tile(q, &few) < few_tiles_cost(L.tile, splits, kps, p.Kg)) {
+        L.tile = few;
+        p.splits = splits = 1;
+        p.k_tiles_per_split = kps = (p.Kg + kKPad - 1) / kKPad;
+      }
+    }
     {
       // Built-in choice between the kernels.  Many tiles: the cheapest
       // conv_pipe tile, or for a 3x3 stride-1 conv the windowed kernel
@@ -1335,7 +1394,6 @@ void Planner::plan_node(int ni) {
       // =0 never; a forced tile decides alone.
       const bool forced = L.tile.halo == 2;
       const char* he = std::getenv("BYOC_CONV_HALO");
-      const bool builtin = !std::getenv("BYOC_CONV_TILE") && !std::getenv("BYOC_CONV_SPLIT");
       const bool many = builtin && splits == 1 && L.tile.kgroups == 1 && conv_pipe_ok(p) &&
                         ((p.M + 63) / 64) * (int64_t)((Kp + 63) / 64) > 256;
       ConvTile pipe{};
@@ -1383,7 +1441,7 @@ void Planner::plan_node(int ni) {
         p.k_tiles_per_split = kps;
       }
     }
-    p.xcd_py = L.tile.stages > 0 ? choose_xcd_split(p, L.tile) : 0;
+    p.xcd_py = L.tile.stages > 0 || L.tile.few ? choose_xcd_split(p, L.tile) : 0;
     L.tile_default = L.tile;
     L.op = Launch::ConvMfma;
     L.info.kind = BYOC_K_CONV_MFMA;
@@ -2062,6 +2120,7 @@ hipError_t exec(const Launch& L, const RunCtx& c) {
       p.partial = (float*)c.ptr(L.partial);
       if (L.op == Launch::SplitReduce) return launch_splitk_reduce(p, c.s);
       if (L.tile.halo) return launch_conv_halo(p, L.tile.bm, L.tile.bn, L.tile.stages, L.tile.lp, L.tile.npb, c.s);
+      if (L.tile.few) return launch_conv_few(p, L.tile.bm, L.tile.bn, c.s);
       if (L.tile.pipe) return launch_conv_pipe(p, L.tile.bm, L.tile.bn, L.tile.stages, L.tile.threads, c.s);
       return L.tile.stages > 0
                  ? launch_conv_dma(p, L.tile.bm, L.tile.bn, L.tile.stages, L.tile.threads, L.tile.kgroups, c.s)
@@ -2539,6 +2598,16 @@ std::vector<ConvTile> conv_candidates(const Launch& L) {
     if (conv_pipe_ok(L.conv)) pipe_tiles();
     return c;
   }
+  if (L.tile_default.few) {  // conv_few's tiles
+    for (int bm : {16, 32})
+      for (int bn : {16, 32}) {
+        ConvTile t = L.tile_default;
+        if (bm == t.bm && bn == t.bn) continue;
+        t.bm = bm, t.bn = bn;
+        c.push_back(t);
+      }
+    return c;
+  }
   if (L.conv.splits > 1 || L.tile_default.mf != 16) return c;
   const ConvParams& p = L.conv;
   const int kgr = L.tile_default.kgroups;  // the reduction order class of the built-in choice
@@ -2694,7 +2763,7 @@ void apply_tile(Launch& L, const ConvTile& t) {
     name_conv_i8(L);
     return;
   }
-  L.conv.xcd_py = t.stages > 0 ? choose_xcd_split(L.conv, t) : 0;
+  L.conv.xcd_py = t.stages > 0 || t.few ? choose_xcd_split(L.conv, t) : 0;
   name_conv(L);
 }
 

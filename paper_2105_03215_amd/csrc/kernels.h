@@ -64,6 +64,7 @@ struct ConvTile {
   int lp = 0, npb = 0;
   int bnv = -1;       // fused bottleneck block: the kernel variant
   int pipe = 0;       // 1: conv_pipe kernel (stages = ring depth, threads 256 or 512)
+  int few = 0;        // 1: conv_few kernel
 };
 
 // Tile configurations with a compiled kernel.
@@ -80,6 +81,11 @@ hipError_t launch_conv_dma(const ConvParams& p, int bm, int bn, int stages, int 
 bool conv_pipe_ok(const ConvParams& p, bool i8 = false);
 bool conv_pipe_tile_supported(int bm, int bn, int stages, int threads);
 hipError_t launch_conv_pipe(const ConvParams& p, int bm, int bn, int stages, int threads, hipStream_t s);
+// Few output pixels: tiles of 16 or 32 pixels x 16 or 32 channels, the reduction
+// split over four waves; one summation order for all tiles.  conv_few_ok:
+// Cp % 64 == 0, at most 32 taps, no split-K.
+bool conv_few_ok(const ConvParams& p);
+hipError_t launch_conv_few(const ConvParams& p, int bm, int bn, hipStream_t s);
 // 3x3 stride-1 pad-1 convolution that stages each 64-channel slice of the
 // input window of a tile (its output pixels' rows plus a one-pixel halo) in
 // LDS once and forms all nine taps from it; weights stream per tap through

@@ -40,12 +40,13 @@ import os
 import statistics
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-CONV_KERNELS = ("conv_mfma_kernel", "conv_dma_kernel", "conv_pipe_kernel", "conv_halo_kernel", "stem_conv_maxpool_kernel",
+CONV_KERNELS = ("conv_mfma_kernel", "conv_dma_kernel", "conv_pipe_kernel", "conv_few_kernel",
+                "conv_halo_kernel", "stem_conv_maxpool_kernel",
                 "splitk_reduce_kernel", "dense_rows_kernel", "bottleneck_kernel", "ir_block_kernel")
 RUN_MARKER = "stem_conv_maxpool_kernel"  # one dispatch per run of the ResNet subgraphs
 # kernels compiled for bf16 and for int8 codes: the int8 form has `true` as
 # its last template argument
-DUAL_KERNELS = ("bottleneck_kernel", "conv_halo_kernel", "stem_conv_maxpool_kernel")
+DUAL_KERNELS = ("bottleneck_kernel", "conv_halo_kernel", "conv_pipe_kernel", "stem_conv_maxpool_kernel")
 
 
 def _short(name):
@@ -134,10 +135,10 @@ def _copy_kib(path, counter):
     return statistics.median([v for v in vals if v > 0.5 * big])
 
 
-CONV_SOURCES = ("conv_mfma.hip", "conv_dma.hip", "conv_pipe.hip", "conv_halo.hip", "bottleneck.hip", "ir_block.hip", "lds_dma.h",
+CONV_SOURCES = ("conv_mfma.hip", "conv_dma.hip", "conv_pipe.hip", "conv_few.hip", "conv_halo.hip", "bottleneck.hip", "ir_block.hip", "lds_dma.h",
                 "stem.hip", "dense_rows.hip", "engine.cpp")
 I8_KERNELS = ("conv_i8_kernel", "bottleneck_kernel", "conv_halo_kernel", "stem_conv_maxpool_kernel")
-I8_SOURCES = ("conv_i8.hip", "conv_halo.hip", "bottleneck.hip", "stem.hip", "quant.hip", "quant_epilogue.h", "lds_dma.h",
+I8_SOURCES = ("conv_i8.hip", "conv_pipe.hip", "conv_halo.hip", "bottleneck.hip", "stem.hip", "quant.hip", "quant_epilogue.h", "lds_dma.h",
               "engine.cpp")
 
 

@@ -153,6 +153,14 @@ __device__ __forceinline__ float rescale_f(int a, float m) {
 }
 __device__ __forceinline__ int rescale(int a, float m) { return (int)rescale_f(a, m); }
 
+// Packed codes from float32: put_u8 writes v, an integer of [0, 255], to byte c
+// (a constant of 0 .. 3) of w in the instruction that converts it; codes go
+// through it with 128 added, and the four bytes turn back by ^ kU8ToCode.
+constexpr uint32_t kU8ToCode = 0x80808080u;
+__device__ __forceinline__ uint32_t put_u8(float v, int c, uint32_t w) {
+  return __builtin_amdgcn_cvt_pk_u8_f32(v, c, w);
+}
+
 // Leaky ReLU on an output code: the offset t = v - zy is kept when t >= 0,
 // otherwise it becomes rint(fl32(t * slope)) (ties to even; |t| < 2^24, so
 // the conversion to float32 is exact).

@@ -9,7 +9,7 @@
 // each group straight from registers, as the kernels for narrow or tiny images
 // do, puts 16-byte pieces Cp * 2 bytes apart.  With events around the launch
 // (about 4 us of them its own cost): 16 x 128 x 56 x 56 bf16 to NHWC 17.0 -> 8.9 us,
-// 32 x 512 x 28 x 28 bf16 to codes 21.7 -> 15.7, 32 x 1024 x 14 x 14 codes to f32
+// 32 x 512 x 28 x 28 bf16 to codes 21.7 -> 14.1, 32 x 1024 x 14 x 14 codes to f32
 // 24.5 -> 7.9.
 //
 // LDS row of pixel p: slot g at g ^ key, key = (p ^ (p / 4)) % GT, so that
@@ -39,9 +39,9 @@ __device__ __forceinline__ T from_f32(float v) {
   else return v;
 }
 
-__device__ __forceinline__ uint32_t quantize_code(float v, float inv, int zp) {
-  const float t = fminf(fmaxf(rintf(v * inv), -512.0f), 512.0f);
-  return (uint32_t)clip_i8((int)t + zp) & 0xFFu;
+// (rint(v / S) clamped to [lo, hi] = [-128 - zp, 127 - zp]) + zp + 128; NaN gives code -128.
+__device__ __forceinline__ float quantize_u8(float v, float inv, float lo, float hi, float off) {
+  return fminf(fmaxf(rintf(v * inv), lo), hi) + off;
 }
 
 // The tile of this workgroup: image, first pixel, first channel group.
@@ -95,11 +95,17 @@ __global__ __launch_bounds__(kThreads) void to_nhwc_kernel(LayoutParams p) {
     }
 #pragma unroll
     for (int i = 0; i < PX; ++i) {
-      uint32_t w[4] = {0u, 0u, 0u, 0u};
+      uint32_t w[4];
       if constexpr (CODES) {
+        const float lo = (float)(-128 - p.zp), hi = (float)(127 - p.zp), off = (float)(p.zp + 128);
 #pragma unroll
-        for (int c = 0; c < CH; ++c)
-          if (c0 + c < p.C) w[c >> 2] |= quantize_code(to_f32(v[c][i]), p.scale, p.zp) << (8 * (c & 3));
+        for (int j = 0; j < 4; ++j) {
+          w[j] = kU8ToCode;  // channels past C: code 0
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+            if (c0 + 4 * j + c < p.C) w[j] = put_u8(quantize_u8(to_f32(v[4 * j + c][i]), p.scale, lo, hi, off), c, w[j]);
+          w[j] ^= kU8ToCode;
+        }
       } else if constexpr (sizeof(SrcT) == 2) {
 #pragma unroll
         for (int c = 0; c < CH; c += 2) w[c >> 1] = (uint32_t)v[c][i] | ((uint32_t)v[c + 1][i] << 16);

@@ -53,22 +53,24 @@ __device__ __forceinline__ uint2 finish8_i8(int a[8], const int2* qc, uint2 rv, 
   uint32_t out[2] = {0u, 0u};
   auto put = [&](int c8, int v) { out[c8 >> 2] |= ((uint32_t)v & 0xFFu) << (8 * (c8 & 3)); };
   // The plain and the residual form (one uniform choice for the 8 channels),
-  // in float32: the rescaled terms are integers below 2^21, so their sum and the
-  // clamp relative to zy are exact and one conversion is left.
-  const float lo = (float)(q.lo - q.zy), hi = (float)(q.hi - q.zy);
+  // in float32: the rescaled terms are integers below 2^21, so their sum, the
+  // clamp relative to zy and the offset are exact and one conversion, which also
+  // places the byte, is left.
+  const float lo = (float)(q.lo - q.zy), hi = (float)(q.hi - q.zy), off = (float)(q.zy + 128);
   if (!q.leaky && !q.post) {
     if (!p.res) {
 #pragma unroll
       for (int c8 = 0; c8 < 8; ++c8)
-        put(c8, q.zy + (int)__builtin_amdgcn_fmed3f(rescale_f(a[c8], __int_as_float(qc[c8].y)), lo, hi));
+        out[c8 >> 2] = put_u8(__builtin_amdgcn_fmed3f(rescale_f(a[c8], __int_as_float(qc[c8].y)), lo, hi) + off,
+                              c8 & 3, out[c8 >> 2]);
     } else {
 #pragma unroll
       for (int c8 = 0; c8 < 8; ++c8) {
         const float t = rescale_f(a[c8], __int_as_float(qc[c8].y)) + rescale_f(res_code(c8) - q.zr, q.mr);
-        put(c8, q.zy + (int)__builtin_amdgcn_fmed3f(t, lo, hi));
+        out[c8 >> 2] = put_u8(__builtin_amdgcn_fmed3f(t, lo, hi) + off, c8 & 3, out[c8 >> 2]);
       }
     }
-    return make_uint2(out[0], out[1]);
+    return make_uint2(out[0] ^ kU8ToCode, out[1] ^ kU8ToCode);
   }
 #pragma unroll
   for (int c8 = 0; c8 < 8; ++c8) {

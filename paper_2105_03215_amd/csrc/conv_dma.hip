@@ -46,7 +46,7 @@ constexpr int kCH = kBK / 8;   // 16-byte chunks per tile row
 constexpr int kMaxStages = 4;  // deepest operand ring (deeper rings measured no faster)
 
 template <int BM, int BN, int WM, int WN, int KG, int NS, bool ALIGNED, bool SPLIT>
-__global__ __launch_bounds__(64 * WM * WN * KG) void conv_dma_kernel(ConvParams p) {
+__device__ __forceinline__ void conv_dma_tile(ConvParams p) {
   static_assert(WM * WN == 4 || WM * WN == 8, "4 or 8 waves per reduction group");
   static_assert(KG == 1 || ((KG == 2 || KG == 4) && !SPLIT), "reduction groups");
   constexpr int kNT = 64 * WM * WN;          // threads of one reduction group
@@ -390,6 +390,23 @@ __global__ __launch_bounds__(64 * WM * WN * KG) void conv_dma_kernel(ConvParams 
     epilogue(std::integral_constant<int, 2>{});
 }
 
+template <int BM, int BN, int WM, int WN, int KG, int NS, bool ALIGNED, bool SPLIT>
+__global__ __launch_bounds__(64 * WM * WN * KG) void conv_dma_kernel(ConvParams p) {
+  conv_dma_tile<BM, BN, WM, WN, KG, NS, ALIGNED, SPLIT>(p);
+}
+
+// Independent convs in one launch: blockIdx.y is the conv, blockIdx.x its
+// tile, each tile as in the conv's own launch (same bits).  A conv of few tiles
+// is bound by its chain of stages plus the launch (about 2.5 us between dependent
+// launches) with CUs idle, and convs side by side share both; the sums are in
+// engine.cpp at group_launches.
+template <int BM, int BN, int WM, int WN, int KG, int NS, bool ALIGNED>
+__global__ __launch_bounds__(64 * WM * WN * KG) void grouped_conv_dma_kernel(ConvGroup g) {
+  const ConvParams p = g.p[blockIdx.y];
+  if (outside_group_member<BM, BN>(p)) return;
+  conv_dma_tile<BM, BN, WM, WN, KG, NS, ALIGNED, false>(p);
+}
+
 template <int BM, int BN, int WM, int WN, int KG, int NS>
 hipError_t launch_tile(const ConvParams& p_in, hipStream_t s) {
   ConvParams p = p_in;
@@ -440,6 +457,30 @@ bool conv_dma_tile_supported(int bm, int bn, int stages, int threads, int kgroup
     return (bm == 128 && bn == 128) || (bm == 128 && bn == 64) || (bm == 64 && bn == 128) ||
            (bm == 128 && bn == 256) || (bm == 256 && bn == 128);
   return false;
+}
+
+bool conv_dma_groupable(const ConvParams& p, int bm, int bn, int stages, int threads, int kgroups) {
+  return bm == 64 && bn == 64 && stages == 3 && threads == 512 && kgroups == 2 && p.splits <= 1;
+}
+
+hipError_t launch_conv_dma_group(ConvGroup g, int n, hipStream_t s) {
+  if (n < 1 || n > kConvGroup) return hipErrorInvalidValue;
+  auto aligned = [](const ConvParams& p) { return p.Cp % kBK == 0 && p.R * p.S <= 32; };
+  const dim3 grid = group_grid(g, n, 64, 64);
+  bool all = true;  // a conv of whole stages takes the general loads as well: same stages, same order
+  for (int i = 0; i < n; ++i) {
+    if (g.p[i].splits > 1) return hipErrorInvalidValue;
+    all = all && aligned(g.p[i]);
+  }
+  // three stages leave LDS for one workgroup per CU, two for two of them
+  if ((int)(grid.x / 8 * n) > kXcdSlots) {
+    if (all) grouped_conv_dma_kernel<64, 64, 2, 2, 2, 2, true><<<grid, 512, 0, s>>>(g);
+    else grouped_conv_dma_kernel<64, 64, 2, 2, 2, 2, false><<<grid, 512, 0, s>>>(g);
+  } else {
+    if (all) grouped_conv_dma_kernel<64, 64, 2, 2, 2, 3, true><<<grid, 512, 0, s>>>(g);
+    else grouped_conv_dma_kernel<64, 64, 2, 2, 2, 3, false><<<grid, 512, 0, s>>>(g);
+  }
+  return hipGetLastError();
 }
 
 hipError_t launch_conv_dma(const ConvParams& p, int bm, int bn, int stages, int threads, int kgroups,

@@ -32,7 +32,7 @@ using namespace dma;
 constexpr int kFewWaves = 4;
 
 template <int TM, int TN>
-__global__ __launch_bounds__(64 * kFewWaves) void conv_few_kernel(ConvParams p) {
+__device__ __forceinline__ void conv_few_tile(ConvParams p) {
   constexpr int BM = TM * 16, BN = TN * 16, KG = kFewWaves;
   // steps in flight per wave (144 or 160 registers of operands): a 3x3 of 256
   // channels on 16x16 tiles is one batch of nine
@@ -175,6 +175,26 @@ __global__ __launch_bounds__(64 * kFewWaves) void conv_few_kernel(ConvParams p) 
 }
 
 template <int TM, int TN>
+__global__ __launch_bounds__(64 * kFewWaves) void conv_few_kernel(ConvParams p) {
+  conv_few_tile<TM, TN>(p);
+}
+
+// independent convs in one launch (blockIdx.y: the conv)
+template <int TM, int TN>
+__global__ __launch_bounds__(64 * kFewWaves) void grouped_conv_few_kernel(ConvGroup g) {
+  const ConvParams p = g.p[blockIdx.y];
+  if (outside_group_member<TM * 16, TN * 16>(p)) return;
+  conv_few_tile<TM, TN>(p);
+}
+
+template <int TM, int TN>
+hipError_t launch_group(ConvGroup& g, int n, hipStream_t s) {
+  const dim3 grid = group_grid(g, n, TM * 16, TN * 16);
+  grouped_conv_few_kernel<TM, TN><<<grid, 64 * kFewWaves, 0, s>>>(g);
+  return hipGetLastError();
+}
+
+template <int TM, int TN>
 hipError_t launch_one(const ConvParams& p_in, hipStream_t s) {
   ConvParams p = p_in;
   const int blocks = placed_blocks(p, TM * 16, TN * 16);
@@ -185,6 +205,17 @@ hipError_t launch_one(const ConvParams& p_in, hipStream_t s) {
 }  // namespace
 
 bool conv_few_ok(const ConvParams& p) { return p.Cp % 64 == 0 && p.R * p.S <= 32 && p.splits <= 1 && p.Kp % 4 == 0; }
+
+hipError_t launch_conv_few_group(ConvGroup g, int n, int bm, int bn, hipStream_t s) {
+  if (n < 1 || n > kConvGroup) return hipErrorInvalidValue;
+  for (int i = 0; i < n; ++i)
+    if (!conv_few_ok(g.p[i])) return hipErrorInvalidValue;
+  if (bm == 16 && bn == 16) return launch_group<1, 1>(g, n, s);
+  if (bm == 16 && bn == 32) return launch_group<1, 2>(g, n, s);
+  if (bm == 32 && bn == 16) return launch_group<2, 1>(g, n, s);
+  if (bm == 32 && bn == 32) return launch_group<2, 2>(g, n, s);
+  return hipErrorInvalidValue;
+}
 
 hipError_t launch_conv_few(const ConvParams& p, int bm, int bn, hipStream_t s) {
   if (!conv_few_ok(p)) return hipErrorInvalidValue;

@@ -52,6 +52,12 @@ struct ConvParams {
   uint64_t mg_wp, mg_hp;  // conv_halo: divisors W + 2 and H + 2 (set by its launcher)
 };
 
+// independent convs of one launch, on the same tile
+constexpr int kConvGroup = 4;
+struct ConvGroup {
+  ConvParams p[kConvGroup];
+};
+
 inline uint64_t magic40(int d) { return ((uint64_t(1) << 40) + (uint64_t)d - 1) / (uint64_t)d; }
 
 struct ConvTile {
@@ -86,6 +92,13 @@ hipError_t launch_conv_pipe(const ConvParams& p, int bm, int bn, int stages, int
 // Cp % 64 == 0, at most 32 taps, no split-K.
 bool conv_few_ok(const ConvParams& p);
 hipError_t launch_conv_few(const ConvParams& p, int bm, int bn, hipStream_t s);
+
+// n <= kConvGroup independent convs in one launch, every one of which
+// conv_dma_groupable takes on that tile (64x64 tiles, 3 stages, two groups of 4 waves),
+// or conv_few_ok.  Results are those of the separate launches.
+bool conv_dma_groupable(const ConvParams& p, int bm, int bn, int stages, int threads, int kgroups);
+hipError_t launch_conv_dma_group(ConvGroup g, int n, hipStream_t s);
+hipError_t launch_conv_few_group(ConvGroup g, int n, int bm, int bn, hipStream_t s);
 // 3x3 stride-1 pad-1 convolution that stages each 64-channel slice of the
 // input window of a tile (its output pixels' rows plus a one-pixel halo) in
 // LDS once and forms all nine taps from it; weights stream per tap through

@@ -162,31 +162,30 @@ void set_few_tile(ConvTile* t, int bm, int bn) {
   *t = ConvTile{};
   t->bm = bm;
   t->bn = bn;
-  t->kgroups = 4;  // (the four waves are its reduction groups)
   t->few = 1;
 }
 
 // conv_few's tile and modelled time (us) for a layer: the largest tile that
-// still makes 180 workgroups, else the smallest; a launch with its prologue and epilogue
-// costs about 4 us and a CU takes in operands at 26 us per MB.  Measured on MI355X,
-// us per layer (modelled): 64 -> 64 3x3 at 56x56 5.5 (5.9), 128 -> 128 at 28x28
-// 6.1 (6.8), 256 -> 256 at 14x14 7.1 (7.8), batch 4 11.5 (11.5), 512 -> 512 at 7x7
-// 11.3 (11.5), batch 8 19.0 (19.0).
+// still makes 180 workgroups, or twice that where a workgroup is one wave (one
+// segment), else the smallest; a launch with its prologue and epilogue costs
+// about 4 us and a CU takes in operands at 26 us per MB.
 double choose_few_tile(const ConvParams& p, ConvTile* t) {
   auto groups = [&](int bm, int bn) { return ((p.M + bm - 1) / bm) * (int64_t)((p.Kp + bn - 1) / bn); };
+  const int enough = p.few_segs > 1 ? 180 : 360;
   int bm = 16, bn = 16;
-  if (groups(32, 32) >= 180) bm = bn = 32;
-  else if (groups(16, 32) >= 180) bn = 32;
+  if (groups(32, 32) >= enough) bm = bn = 32;
+  else if (groups(16, 32) >= enough) bn = 32;
   set_few_tile(t, bm, bn);
   const double mb = (double)((groups(bm, bn) + 255) / 256) * (bm + bn) * p.Kg * 2.0 / (1 << 20);
   return 4.0 + 26.0 * mb;
 }
 
-// The time of what choose_conv_tile chose for a layer of few 64x64 tiles, measured
-// the same way: split-K with its reduce launch 8 us + 0.34 per stage of a
-// split (256 -> 256 at 14x14 9.9, modelled 9.7; batch 4 12.4, 12.1; 512 -> 512 at 7x7
-// 10.3, 9.7), four reduction groups 6.6 + 0.34 per stage of a group (64 -> 64
-// at 56x56 7.6, 7.6), one 64x64 tile per workgroup 5.5 + 0.25 per stage.
+// The time of what choose_conv_tile chose for a layer of few 64x64 tiles, on
+// the same scale (about 1 us below the chain's times, as above): split-K with its reduce launch
+// 8 us + 0.34 per stage of a split (256 -> 256 at 14x14 11.0, modelled 9.7; batch
+// 4 13.2, 12.1; 512 -> 512 at 7x7 11.5, 9.7), reduction groups 6.6 + 0.34 per stage of
+// a group (64 -> 64 at 56x56 8.5, 7.6), one 64x64 tile per workgroup 5.5 + 0.25 per
+// stage (64 -> 64 1x1 at 28x28 4.6, 5.8; 448 -> 448 at 8x8, batch 4, 7.0, 7.3).
 double few_tiles_cost(const ConvTile& t, int splits, int kps, int Kg) {
   const int nk = (Kg + kKPad - 1) / kKPad;
   if (splits > 1) return 8.0 + 0.34 * kps;
@@ -315,8 +314,8 @@ void name_conv(Launch& L) {
     std::snprintf(L.info.name, sizeof(L.info.name), "conv_halo_%dx%d_s%d_lp%d_pb%d", L.tile.bm, L.tile.bn,
                   L.tile.stages, L.tile.lp, L.tile.npb);
   else if (L.tile.few)
-    std::snprintf(L.info.name, sizeof(L.info.name), "conv_few_%dx%d_k%d_w%d", L.tile.bm, L.tile.bn, L.tile.kgroups,
-                  L.tile.threads / 64);
+    std::snprintf(L.info.name, sizeof(L.info.name), "conv_few_%dx%d_k%d_w%d", L.tile.bm, L.tile.bn, L.conv.few_segs,
+                  conv_few_waves(L.conv, L.tile.bm, L.tile.bn));
   else if (L.tile.pipe)
     std::snprintf(L.info.name, sizeof(L.info.name), "conv_pipe_%dx%d_s%d_w%d", L.tile.bm, L.tile.bn, L.tile.stages,
                   L.tile.threads / 64);
@@ -1353,11 +1352,15 @@ void Planner::plan_node(int ni) {
     }
     int splits, kps;
     choose_conv_tile(p.M, Kp, p.Kg, &L.tile, &splits, &kps);
+    ConvParams few = p;  // as conv_few takes the layer: this plan's sums, without split-K
+    few.splits = 1;
+    few.few_segs = splits > 1 ? splits : L.tile.kgroups;
+    few.k_tiles_per_split = L.tile.kgroups > 1 ? 0 : kps;
     apply_tile_override(p.Kg, &L.tile, &splits, &kps);
     if (L.tile.pipe == 2 || L.tile.few == 2) {  // a forced conv_pipe or conv_few tile forgoes split-K
       ConvParams q = p;
       q.splits = 1;
-      if (L.tile.few ? conv_few_ok(q) : conv_pipe_ok(q)) {
+      if (L.tile.few ? conv_few_ok(few) : conv_pipe_ok(q)) {
         (L.tile.few ? L.tile.few : L.tile.pipe) = 1;
         splits = 1;
         kps = (p.Kg + kKPad - 1) / kKPad;
@@ -1371,15 +1374,13 @@ void Planner::plan_node(int ni) {
     const bool builtin = !std::getenv("BYOC_CONV_TILE") && !std::getenv("BYOC_CONV_SPLIT");
     // few 64x64 tiles: conv_few, where its modelled time is less
     if (builtin && ((p.M + 63) / 64) * (int64_t)((Kp + 63) / 64) <= 64) {
-      ConvParams q = p;
-      q.splits = 1;
-      ConvTile few{};
-      if (conv_few_ok(q) && choose_few_tile(q, &few) < few_tiles_cost(L.tile, splits, kps, p.Kg)) {
-        L.tile = few;
-        p.splits = splits = 1;
-        p.k_tiles_per_split = kps = (p.Kg + kKPad - 1) / kKPad;
+      ConvTile t{};
+      if (conv_few_ok(few) && choose_few_tile(few, &t) < few_tiles_cost(L.tile, splits, kps, p.Kg)) {
+        L.tile = t;
+        splits = 1;
       }
     }
+    if (L.tile.few) p = few;
     {
       // Built-in choice between the kernels.  Many tiles: the cheapest
       // conv_pipe tile, or for a 3x3 stride-1 conv the windowed kernel

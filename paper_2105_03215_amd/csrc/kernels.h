@@ -38,6 +38,7 @@ struct ConvParams {
   int w_bytes;
   int res_bytes;
   int res_post;  // 1: the residual is added after the activation, to its bf16-rounded value
+  int few_segs;  // conv_few: accumulators of an output (of k_tiles_per_split steps each, or 0: interleaved)
   int slice_major;  // conv_pipe: 1 sums 64-channel slices outermost, taps inside (conv_halo's order), 0 taps outermost
   // conv_dma tile placement: > 0 splits the tile grid into (8 / xcd_py) x
   // xcd_py blocks along (pixels, channels), one per XCD, so that an XCD's L2
@@ -88,9 +89,11 @@ bool conv_pipe_ok(const ConvParams& p, bool i8 = false);
 bool conv_pipe_tile_supported(int bm, int bn, int stages, int threads);
 hipError_t launch_conv_pipe(const ConvParams& p, int bm, int bn, int stages, int threads, hipStream_t s);
 // Few output pixels: tiles of 16 or 32 pixels x 16 or 32 channels, the reduction
-// split over four waves; one summation order for all tiles.  conv_few_ok:
-// Cp % 64 == 0, at most 32 taps, no split-K.
+// split over the waves of a workgroup; the sums of the plan that few_segs and
+// k_tiles_per_split describe.  conv_few_ok: Cp % 64 == 0, at most 32 taps,
+// no split-K, a plan of at most 16 segments.
 bool conv_few_ok(const ConvParams& p);
+int conv_few_waves(ConvParams p, int bm, int bn);  // of a workgroup in its own launch
 hipError_t launch_conv_few(const ConvParams& p, int bm, int bn, hipStream_t s);
 
 // n <= kConvGroup independent convs in one launch, every one of which

@@ -62,3 +62,40 @@ def test_built_in_choice(n, c, hw, k, r):
             torch.cuda.synchronize()
     assert torch.equal(outs[False].view(torch.int16), outs[True].view(torch.int16))
     assert within_one_ulp(runtime.to_host_f64(outs[False]), ref, term_scale_graph(wl.graph, wl.consts, wl.inputs)[0]).all()
+
+
+@pytest.mark.parametrize("n,c,hw,k,r,segs,plan", [
+    (1, 256, 14, 256, 3, 8, {"BYOC_CONV_SPLIT": "8"}),         # a split per wave, the last of one step
+    (1, 512, 7, 512, 3, 15, {"BYOC_CONV_SPLIT": "16"}),        # two per wave, one left over
+    (1, 1024, 5, 40, 1, 4, {"BYOC_CONV_SPLIT": "4"}),
+    (3, 1024, 3, 256, 3, 16, {"BYOC_CONV_SPLIT": "16"}),       # more steps of a wave than it holds in flight
+    (1, 64, 56, 64, 3, 4, {"BYOC_CONV_TILE": "d64x64s2t1024k4"}),  # four interleaved groups, shares of 3, 2, 2, 2 steps
+    (8, 512, 8, 512, 1, 2, {"BYOC_CONV_TILE": "d64x64s3t512k2"}),  # two interleaved groups
+    (1, 256, 56, 64, 1, 1, {"BYOC_CONV_SPLIT": "1"}),          # one accumulator
+])
+def test_sums_of_the_plan_it_replaces(n, c, hw, k, r, segs, plan, monkeypatch):
+    """Bit for bit the split-K, reduction-group or plain plan that the layer would
+    have, on every tile, with residual and bias."""
+    g = GraphBuilder("few_plan", 6200 + c + k)
+    x = g.input("x", [n, c, hw, hw])
+    res = g.input("res", [n, k, hw, hw])
+    g.output(g.conv(x, k, r, act="relu", residual=res, name="y"))
+    wl = g.finish()
+
+    def run(env):
+        announce("conv_few against %s: %s" % (plan, env))
+        with monkeypatch.context() as mp:
+            for key, v in env.items():
+                mp.setenv(key, v)
+            with capi.Subgraph(wl.graph, wl.consts, device=0) as sg:
+                out = runtime.outputs_for(sg, DEV)[0].fill_(float("nan"))
+                sg.run(runtime.inputs_for(sg, wl.inputs, DEV), [out])
+                torch.cuda.synchronize()
+                return out.view(torch.int16), [l["name"] for l in sg.launches() if l["kind"] == "conv_mfma"][0]
+
+    ref, name = run(plan)
+    assert not name.startswith("conv_few"), name
+    for tile in TILES:
+        out, name = run({"BYOC_CONV_TILE": tile})
+        assert name.startswith("conv_few") and "_k%d_" % segs in name, name
+        assert torch.equal(out, ref), name

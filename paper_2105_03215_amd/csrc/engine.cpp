@@ -1385,10 +1385,12 @@ void Planner::plan_node(int ni) {
       // Built-in choice between the kernels.  Many tiles: the cheapest
       // conv_pipe tile, or for a 3x3 stride-1 conv the windowed kernel
       // (conv_halo: the input window staged in LDS once per 64-channel slice)
-      // if its modelled time is less - it wins while its 128x64 tiles make about one
-      // round (256 channels at 14x14, batch 32: 196 tiles, 13 against 20 us;
-      // 128 -> 256 channels at 32x32, batch 8: 12.7 against 14.8) and loses
-      // with more (512 channels at 28x28, batch 32: 153 against 113 us).
+      // if it has 256 channels or more and its modelled time is less - it wins
+      // while its 128x64 tiles make about one round (256 channels at 14x14, batch 32:
+      // 196 tiles, 13 against 20 us) and loses with more (512 channels at 28x28,
+      // batch 32: 153 against 113 us).  Under 256 channels the sums run tap by tap on every
+      // kernel but this one, which therefore stays out, although 128 -> 256 channels at
+      // 32x32, batch 8, would take 12.7 us in place of 14.8.
       // Where 128x64 tiles are too few for that but 64x64 ones are
       // enough (512 channels at 7x7: 200 tiles) it runs on 64x64 tiles.
       // BYOC_CONV_HALO=1 takes the windowed kernel wherever the shape allows,
@@ -1404,7 +1406,7 @@ void Planner::plan_node(int ni) {
       // (wherever the windowed kernel is the 3x3 layer's kernel by its own
       // rule, conv_pipe takes over its summation order with it)
       const bool halo_class = Cp >= 256 && halo_tiles >= 160;
-      const bool by_rule = many ? halo_tiles >= 160 && Cp >= 128 && tile_cost(kHaloCost, p) < pipe_cost : halo_class;
+      const bool by_rule = halo_class && (!many || tile_cost(kHaloCost, p) < pipe_cost);
       const bool by_rule64 = Cp >= 256 && halo_tiles < 160 && halo64_tiles >= 160;
       const bool want = forced || (!std::getenv("BYOC_CONV_TILE") && (he ? he[0] == '1' : by_rule || by_rule64));
       if (many) {

@@ -116,6 +116,27 @@ def test_built_in_choice_over_many_tiles(n, c, hw, k, r, monkeypatch):
         assert (abs(a - b) <= 2.0 ** -7 * abs(b) + 1e-4).all()
 
 
+@pytest.mark.parametrize("n,c,hw,k", [(8, 128, 32, 256), (16, 192, 14, 512), (10, 64, 32, 256)])
+def test_sums_tap_by_tap_under_256_channels(n, c, hw, k, monkeypatch):
+    """3x3 layers of fewer channels than the windowed kernel's rule asks for keep the
+    64x64 tile's bits, whatever kernel has the least modelled time."""
+    g = GraphBuilder("pipe_tap_order", 4400 + c)
+    g.output(_conv(g, (n, c, hw, hw), k, 3, act="leaky"))
+    wl = g.finish()
+    first, _ = _run(wl, "d64x64s2t256k1", monkeypatch)
+    monkeypatch.delenv("BYOC_CONV_TILE")
+    monkeypatch.delenv("BYOC_CONV_SPLIT")
+    with capi.Subgraph(wl.graph, wl.consts, device=0) as sg:
+        ins = runtime.inputs_for(sg, wl.inputs, DEV)
+        for tuned in (False, True):
+            announce("tap order %s tuned %s" % ((n, c, hw, k), tuned))
+            sg.set_options(autotune=tuned)
+            out = runtime.outputs_for(sg, DEV)[0].fill_(float("nan"))
+            sg.run(ins, [out])
+            torch.cuda.synchronize()
+            assert torch.equal(out.view(torch.int16), first.view(torch.int16)), [l["name"] for l in sg.launches()]
+
+
 def test_windowed_kernels_order_is_shared():
     """A 3x3 layer of the windowed kernel's class that conv_pipe takes over
     keeps the windowed kernel's bits, before and after tuning."""

@@ -106,26 +106,31 @@ void choose_conv_tile(int64_t M, int Kp, int Kg, ConvTile* t, int* splits, int* 
 
 // Launches with more 64x64 tiles than CUs (choose_conv_tile's plain 64x64
 // case): the tile whose modelled time is least.  A tile's workgroups run in
-// rounds of occ per CU; a round costs a fixed part (prologue, first fills,
-// epilogue, drain) and, per 64-deep stage, the time of as many co-resident
-// workgroups as its CUs hold.  The numbers are us measured on MI355X over dense layers
-// of 784-50176 rows, 256-3072 channels and reductions of 256-2304, and
-// agree with the measured times to about 10%: 12544 x 1024 x 2304 104 us on
-// 64x64 tiles, 58.7 on 256x256 (modelled 53), 65.9 on 128x128; 6272 x 1024 x 2304
-// 55.8, 51.3 and 35.7; 50176 x 256 x 1024 49.2, 33.2 and 36.8.  A GELU
+// rounds of occ per CU; a launch costs kLaunchCost, a round a fixed part
+// (first fills, epilogue, drain) and, per 64-deep stage, the time of as many co-resident
+// workgroups as its CUs hold.  The numbers are us, fitted to the layers of chains of
+// four replayed as a graph on MI355X: dense of 640-50176 rows by 256-2048 channels and 3x3
+// convs of 64-512 channels with 196-1568 128x64 tiles.  Over these the model is within 3% at the
+// median, 10% at nine of ten and 20% at all but one, and its choice costs at most 9% over the
+// best tile: measured (modelled) on 256x256, 128x128 and 64x64 tiles, 12544 x 1024 x 1024 35.0
+// (30.3), 39.0 (39.1), 52.3 (53.5); 4096 x 1024 x 1024 29.7 (30.3), 17.5 (16.9),
+// 21.3 (22.0); 3x3 512 -> 512 at 14x14, batch 24, 94.2 (95.8), 51.5 (51.6), 44.9 (46.3), on
+// the windowed kernel 41.8 (44.0).  The one: 320 -> 320 at 28x28, batch 8, on the windowed
+// kernel 31.0 (18.0), 31 of its workgroups on an XCD.  A GELU
 // epilogue adds its vector-ALU time, which a single workgroup per CU cannot overlap.
 struct PipeCost {
   int bm, bn, threads, stages, occ;
   double fixed, stage[3], gelu;
 };
+constexpr double kLaunchCost = 5.0;
 constexpr PipeCost kPipeCost[] = {
-    {256, 256, 512, 2, 1, 8.0, {1.25}, 12.0},          {256, 128, 512, 3, 1, 6.8, {0.77}, 6.0},
-    {128, 256, 512, 3, 1, 6.5, {0.76}, 6.0},           {128, 192, 512, 3, 1, 6.5, {0.62}, 4.5},
-    {128, 128, 512, 2, 2, 6.0, {0.36, 0.74}, 4.0},     {128, 64, 256, 3, 2, 5.0, {0.33, 0.53}, 1.5},
-    {64, 128, 256, 3, 2, 5.0, {0.31, 0.53}, 1.5},      {64, 64, 256, 3, 3, 4.5, {0.23, 0.34, 0.48}, 1.0},
+    {256, 256, 512, 2, 1, 6.6, {1.17}, 12.0},          {256, 128, 512, 3, 1, 4.5, {0.77}, 6.0},
+    {128, 256, 512, 3, 1, 3.7, {0.79}, 6.0},           {128, 192, 512, 3, 1, 3.4, {0.61}, 4.5},
+    {128, 128, 512, 2, 2, 2.0, {0.62, 0.94}, 4.0},     {128, 64, 256, 3, 2, 2.5, {0.45, 0.58}, 1.5},
+    {64, 128, 256, 3, 2, 2.4, {0.44, 0.58}, 1.5},      {64, 64, 256, 3, 3, 1.7, {0.30, 0.46, 0.55}, 1.0},
 };
 // (the windowed 3x3 kernel's 128x64 tile, one workgroup per CU)
-constexpr PipeCost kHaloCost = {128, 64, 512, 3, 1, 3.0, {0.24}, 1.5};
+constexpr PipeCost kHaloCost = {128, 64, 512, 3, 1, 2.2, {0.24}, 1.5};
 
 double tile_cost(const PipeCost& c, const ConvParams& p, int stage = kKPad) {
   constexpr int kCus = 256;
@@ -133,7 +138,7 @@ double tile_cost(const PipeCost& c, const ConvParams& p, int stage = kKPad) {
   const int st = (p.Kg + stage - 1) / stage;
   const double fixed = c.fixed + (p.act == kActGelu ? c.gelu : 0.0);
   const int64_t full = tiles / (kCus * c.occ), rest = tiles % (kCus * c.occ);
-  double t = (double)full * (fixed + st * c.stage[c.occ - 1]);
+  double t = kLaunchCost + (double)full * (fixed + st * c.stage[c.occ - 1]);
   if (rest > 0) t += fixed + st * c.stage[(rest + kCus - 1) / kCus - 1];
   return t;
 }
@@ -1386,9 +1391,9 @@ void Planner::plan_node(int ni) {
       // conv_pipe tile, or for a 3x3 stride-1 conv the windowed kernel
       // (conv_halo: the input window staged in LDS once per 64-channel slice)
       // if it has 256 channels or more and its modelled time is less - it wins
-      // while its 128x64 tiles make about one round (256 channels at 14x14, batch 32:
-      // 196 tiles, 13 against 20 us) and loses with more (512 channels at 28x28,
-      // batch 32: 153 against 113 us).  Under 256 channels the sums run tap by tap on every
+      // while its 128x64 tiles make one or two rounds (256 channels at 14x14, batch 32:
+      // 196 tiles, 15.7 against 22.8 us; 512 at 14x14, batch 32: 392 tiles, 43.7 against 47.9)
+      // and loses with more (512 channels at 28x28, batch 16: 784 tiles, 82 against 66 us).  Under 256 channels the sums run tap by tap on every
       // kernel but this one, which therefore stays out, although 128 -> 256 channels at
       // 32x32, batch 8, would take 12.7 us in place of 14.8.
       // Where 128x64 tiles are too few for that but 64x64 ones are

@@ -271,7 +271,7 @@ hipError_t launch_conv_f32_mfma(const ConvF32Params& p_in, hipStream_t s) {
   ConvF32Params p = p_in;
   const int64_t M = (int64_t)p.N * p.P * p.Q;
   if (M == 0 || p.K == 0) return hipSuccess;
-  const bool rows = p.H == 1 && p.W == 1 && p.R == 1 && p.S == 1 && p.P == 1 && p.Q == 1;
+  if (!p.rows && !p.taps) return hipErrorInvalidValue;
   p.vec4 = p.C % 4 == 0 && (uintptr_t)p.x % 16 == 0;
   p.vec4_out = p.K % 4 == 0 && (uintptr_t)p.y % 16 == 0 && (uintptr_t)p.res % 16 == 0;
   // The smallest tiles that still make work for the whole chip once or
@@ -283,7 +283,7 @@ hipError_t launch_conv_f32_mfma(const ConvF32Params& p_in, hipStream_t s) {
   // 33 | 91; 1000 x 512 x 1500 35 | 29 | 34 | 55; 300 x 768 x 2048 37 | 28 | 22 | 33;
   // 30 x 768 x 3072 30 | 21 | 11 | 8.4.
   auto tiles = [&](int bm, int bn) { return (M + bn - 1) / bn * ((p.K + bm - 1) / bm); };
-  if (rows) {
+  if (p.rows) {
     if (tiles(64, 64) >= 600) return launch_tile<64, 64, 2, 2, 1, true>(p, s);
     if (tiles(64, 32) >= 400) return launch_tile<64, 32, 2, 1, 2, true>(p, s);
     if (tiles(32, 32) >= 200) return launch_tile<32, 32, 2, 2, 2, true>(p, s);

@@ -1243,12 +1243,13 @@ void Planner::plan_node(int ni) {
       p.sh = n.stride[0], p.sw = n.stride[1], p.pt = n.pad[0], p.pl = n.pad[1];
       p.groups = n.groups, p.act = (int)n.act;
       p.alpha = n.alpha;
+      p.rows = R == 1 && S == 1 && H == 1 && W == 1 && P == 1 && Q == 1 && p.pt == 0 && p.pl == 0;
       if (conv_f32_mfma_ok(p)) {  // the matrix-core kernel, its weight rows padded
         const int crs = Cg * R * S, rows = (int)rup(K, 64);
         p.ldw = (int)rup(crs, 256);
         L.w = wslot((int64_t)rows * p.ldw * 4);
         jobs.push_back({PackJob::RowsW32, wc, L.w.off, K, 0, 0, 0, 0, p.ldw, rows, crs, 0});
-        if (!(H == 1 && W == 1 && R == 1 && S == 1)) {
+        if (!p.rows) {
           std::vector<uint8_t> b((size_t)p.ldw * sizeof(F32Tap), 0);
           F32Tap* t = reinterpret_cast<F32Tap*>(b.data());
           for (int kk = 0; kk < crs; ++kk) {

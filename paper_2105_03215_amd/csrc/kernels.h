@@ -256,7 +256,10 @@ struct ConvF32Params {
   int N, C, H, W, K, P, Q, R, S, sh, sw, pt, pl, groups, act;
   float alpha;  // leaky ReLU slope
   int ldw;      // > 0: weight row stride (multiple of 256 floats), the matrix-core kernel
-  const F32Tap* taps;    // [ldw] (images; not read for a dense layer)
+  // a plain matrix product: 1x1 taps on 1x1 maps, no padding (a padded 1x1 map
+  // may put the tap outside it); otherwise the matrix-core kernel needs `taps`
+  bool rows;
+  const F32Tap* taps;    // [ldw], unless rows
   bool vec4, vec4_out;   // (set by its launcher: aligned 16-byte accesses of a dense layer)
 };
 hipError_t launch_conv_f32(const ConvF32Params& p, hipStream_t s);

@@ -60,3 +60,42 @@ def test_dense(case):
     r = g.input("r", [m, n], "normal") if res else None
     g.output(g.dense(x, n, act=act, residual=r, w_std=0.05, name="y"))
     _check(g.finish(), kin, "dense %s" % (case,))
+
+
+@pytest.mark.parametrize("pad,stride", [(1, 1), (1, 2), (1, 3), ([1, 0, 0, 0], 2), ([0, 1, 0, 0], 2), ([0, 0, 1, 1], 2),
+                                        ([0, 0, 1, 0], 1)], ids=str)
+def test_1x1_conv_of_padded_1x1_map(pad, stride):
+    """A 1x1 map with padding is no plain matrix product: outputs beside the pixel are the bias."""
+    g = GraphBuilder("f32_padded_pixel", 5200, dtype="f32")
+    g.output(g.conv(g.input("x", [3, 37, 1, 1], "normal"), 21, 1, stride=stride, pad=pad, act=None, name="y"))
+    _check(g.finish(), 37, "padded 1x1 map %s %s" % (pad, stride))
+
+
+def test_infinities_and_denormals():
+    """Infinities reach the outputs that read them and no others; denormal products count."""
+    g = GraphBuilder("f32_special", 5300, dtype="f32")
+    x = g.input("x", [2, 40, 9, 8], "normal")
+    g.output(g.conv(x, 20, 3, bn=False, act=None, name="y"))
+    wl = g.finish()
+    w = next(i for i, c in enumerate(wl.graph["constants"]) if len(c["shape"]) == 4)
+    xs, ws = wl.inputs[0].copy(), [np.array(c) for c in wl.consts]
+    xs[0, 3, 4, 4], xs[0, 7, 0, 0], xs[1, 39, 8, 7] = np.inf, -np.inf, -np.inf
+    ws[w][np.abs(ws[w]) < 1e-3] = 1e-3  # (no zero times infinity)
+    announce("fp32 infinities")
+    ref = oracle.run_graph(wl.graph, ws, [xs], mode="exact")[0]
+    with capi.Subgraph(wl.graph, ws, device=0) as sg:
+        out = runtime.outputs_for(sg, DEV)
+        sg.run([torch.from_numpy(xs).to(DEV)], out)
+        got = runtime.to_host_f64(out[0])
+        special = ~np.isfinite(ref)
+        assert special.any() and not special.all()
+        assert np.array_equal(got[special], ref[special])
+        assert np.allclose(got[~special], ref[~special], rtol=1e-4, atol=1e-4)
+        # products around 2^-136, sums of 360 of them below the normal range
+        tiny = np.full_like(xs, 2.0 ** -126)
+        sg2 = capi.Subgraph(wl.graph, [np.full_like(c, 2.0 ** -10) if c.ndim == 4 else np.zeros_like(c) for c in ws], device=0)
+        sg2.run([torch.from_numpy(tiny).to(DEV)], out)
+        torch.cuda.synchronize()
+        mid = out[0].double().cpu().numpy()[:, :, 1:-1, 1:-1]
+        sg2.close()
+        assert (mid == 360 * 2.0 ** -136).all(), mid.flat[0] / 2.0 ** -136

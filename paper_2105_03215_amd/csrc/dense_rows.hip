@@ -111,8 +111,9 @@ __global__ __launch_bounds__(kThreads) void dense_rows_kernel(ConvParams p) {
 }  // namespace
 
 bool dense_rows_supported(const ConvParams& p) {
+  // (no padding: with it the one tap of a 1x1 map may lie outside it)
   return p.M >= 1 && p.M <= 64 && p.R == 1 && p.S == 1 && p.H == 1 && p.W == 1 && p.P == 1 && p.Q == 1 &&
-         p.splits == 1 && p.Kp % 4 == 0 && p.Kgp % 64 == 0;
+         p.pt == 0 && p.pl == 0 && p.splits == 1 && p.Kp % 4 == 0 && p.Kgp % 64 == 0;
 }
 
 hipError_t launch_dense_rows(const ConvParams& p, hipStream_t s) {

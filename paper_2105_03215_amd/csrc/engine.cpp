@@ -1341,9 +1341,8 @@ void Planner::plan_node(int ni) {
     // the dense-rows kernel, one workgroup per 16 output channels with the
     // reduction split over its waves; BYOC_DENSE_ROWS=0 (or a forced conv
     // tile) keeps the conv kernels
-    const bool rows_gemm = R == 1 && S == 1 && H == 1 && W == 1 && P == 1 && Q == 1;
     const char* dr_env = std::getenv("BYOC_DENSE_ROWS");
-    if (rows_gemm && p.M <= 64 && !std::getenv("BYOC_CONV_TILE") && !(dr_env && dr_env[0] == '0')) {
+    if (!std::getenv("BYOC_CONV_TILE") && !(dr_env && dr_env[0] == '0')) {
       p.splits = 1;
       p.k_tiles_per_split = p.Kgp / kKPad;
       if (dense_rows_supported(p)) {

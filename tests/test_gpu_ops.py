@@ -364,6 +364,15 @@ def test_f32_single_composite_config():
     _check_f32(workloads.conv_f32(), "conv_f32 1x16x32x32 -> 32")
 
 
+@pytest.mark.parametrize("pad,stride", [(1, 1), (1, 3), ([1, 0, 0, 0], 2), ([0, 0, 1, 1], 2)], ids=str)
+def test_1x1_conv_of_padded_1x1_map(pad, stride):
+    """A 1x1 map with padding is no plain matrix product: its one tap may lie outside."""
+    g = GraphBuilder("op_padded_pixel", 1540)
+    g.output(g.conv(g.input("x", [3, 64, 1, 1], "normal"), 40, 1, stride=stride, pad=pad, act="relu", name="y"))
+    launches = _check_bf16(g.finish(), "padded 1x1 map %s %s" % (pad, stride))
+    assert (pad == [0, 0, 1, 1]) == any(l["name"].startswith("dense_rows") for l in launches), launches
+
+
 F32_CONV_CASES = [
     # name, (n, c, h, w), k, r, stride, pad, act, residual: the
     # register-blocked kernel (3x3 and 1x1: odd channel counts, output

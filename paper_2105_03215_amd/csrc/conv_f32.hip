@@ -1,9 +1,12 @@
 // fp32 convolution on the vector ALU, for what the matrix-core kernel does not
-// take (grouped convs, more than 32 taps, inputs of 2 GiB and more): direct
+// take (grouped convs, more than 32 taps, inputs of 2 GiB and more) and for images
+// of many pixels with few output channels: direct
 // NCHW evaluation of the conv composite, one thread per output, fused multiply-adds in fp32 over the
 // reduction in (c, r, s) order, then bias, residual, activation.  Dense runs
 // as the 1x1 case on [M, K, 1, 1]; consecutive threads take
 // consecutive output columns so input rows are read contiguously.
+#include <algorithm>
+
 #include "device_common.h"
 
 namespace byoc {
@@ -119,21 +122,43 @@ __global__ __launch_bounds__(64) void conv_f32_regs_kernel(ConvF32Params p) {
   }
 }
 
+bool regs_ok(const ConvF32Params& p) {
+  return p.groups == 1 && (int64_t)p.N * ((p.K + kKB - 1) / kKB) <= 65535 && (int64_t)p.P * p.Q < (int64_t(1) << 30) &&
+         (int64_t)p.C * p.H * p.W < (int64_t(1) << 31) && p.R == p.S && (p.R == 3 || p.R == 1);
+}
+
 }  // namespace
+
+// The matrix-core kernel's tile for many pixels has 32 channels, all of which it
+// pays for, and takes the reduction in stages of 32: with few output channels or a short
+// reduction the kernels above are faster.  The modelled times are us per million
+// pixels on MI355X, plus a part per input channel or tap (their serial chain of loads) and
+// per stage.  With events around the launch, measured (modelled) here | on the matrix cores,
+// 16 x 224 x 224 3x3: 3 -> 1 11.7 (17.0) | 51.7 (51.6), 3 -> 16 42.2 (42.4) | 69.7 (70.8), 3 -> 32 79.1
+// (79.8) | 74.7 (74.7); 16 -> 16 117 (125) | 144 (144); 32 -> 16 228 (227) | 225 (217); 1x1: 32 -> 8
+// 37.5 (38.6) | 62.4 (68.8); 5x5: 1 -> 4 47.4 (59.3) | 75.3 (67.8); 2 x 112 x 112 3x3:
+// 8 -> 8 6.7 (7.4) | 8.5 (8.9).  Fewer pixels than the rule asks for run on smaller
+// matrix-core tiles, which were never slower by more than 1 us.
+bool conv_f32_vector_faster(const ConvF32Params& p) {
+  const double pix = (double)p.N * p.P * p.Q, crs = (double)p.C * p.R * p.S;
+  if (p.groups != 1 || p.rows || pix < 64 * 384 || p.K > 64) return false;
+  const int st = (int)((crs + 31) / 32), kg = std::min(p.K, 32);
+  const double mfma =
+      4.0 + 0.6 * st + pix * 1e-6 * ((p.K + 31) / 32) * (30.0 + 6.7 * std::min(kg, 4) + 0.3 * std::max(kg - 4, 0) + 22.0 * st);
+  if (!regs_ok(p)) return 4.5 + 0.04 * crs + pix * 1e-6 * (p.K + 0.4) * (1.5 + 0.55 * crs) < mfma;
+  const double mpix = p.N * (((int64_t)p.P * p.Q + 63) / 64 * 64e-6);  // (64-pixel blocks of an image)
+  const double k4 = (p.K + kKB - 1) / kKB * kKB;
+  return (p.R == 3 ? 4.3 + (0.26 + 0.002 * p.C) * p.C + mpix * std::max(6.0 + 0.33 * crs, k4 * (1.5 + 0.052 * crs))
+                   : 4.3 + 0.075 * p.C + mpix * std::max(5.0 + 0.6 * crs, k4 * (1.4 + 0.11 * crs))) < mfma;
+}
 
 hipError_t launch_conv_f32(const ConvF32Params& p, hipStream_t s) {
   const int64_t total = (int64_t)p.N * p.K * p.P * p.Q;
   if (total == 0) return hipSuccess;
-  const int64_t gy = (int64_t)p.N * ((p.K + kKB - 1) / kKB);
-  const int64_t pix = (int64_t)p.P * p.Q;
-  const bool regs = p.groups == 1 && gy <= 65535 && pix < (int64_t(1) << 30) &&
-                    (int64_t)p.C * p.H * p.W < (int64_t(1) << 31);
-  if (regs && p.R == 3 && p.S == 3) {
-    conv_f32_regs_kernel<3, 3><<<dim3((unsigned)((pix + 63) / 64), (unsigned)gy), 64, 0, s>>>(p);
-    return hipGetLastError();
-  }
-  if (regs && p.R == 1 && p.S == 1) {
-    conv_f32_regs_kernel<1, 1><<<dim3((unsigned)((pix + 63) / 64), (unsigned)gy), 64, 0, s>>>(p);
+  if (regs_ok(p)) {
+    const dim3 grid((unsigned)(((int64_t)p.P * p.Q + 63) / 64), (unsigned)(p.N * ((p.K + kKB - 1) / kKB)));
+    if (p.R == 3) conv_f32_regs_kernel<3, 3><<<grid, 64, 0, s>>>(p);
+    else conv_f32_regs_kernel<1, 1><<<grid, 64, 0, s>>>(p);
     return hipGetLastError();
   }
   conv_f32_kernel<<<(unsigned)((total + 255) / 256), 256, 0, s>>>(p);

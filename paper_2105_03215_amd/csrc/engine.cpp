@@ -1244,7 +1244,7 @@ void Planner::plan_node(int ni) {
       p.groups = n.groups, p.act = (int)n.act;
       p.alpha = n.alpha;
       p.rows = R == 1 && S == 1 && H == 1 && W == 1 && P == 1 && Q == 1 && p.pt == 0 && p.pl == 0;
-      if (conv_f32_mfma_ok(p)) {  // the matrix-core kernel, its weight rows padded
+      if (conv_f32_mfma_ok(p) && !conv_f32_vector_faster(p)) {  // the matrix-core kernel, its weight rows padded
         const int crs = Cg * R * S, rows = (int)rup(K, 64);
         p.ldw = (int)rup(crs, 256);
         L.w = wslot((int64_t)rows * p.ldw * 4);

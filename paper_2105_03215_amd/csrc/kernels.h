@@ -263,6 +263,8 @@ struct ConvF32Params {
   bool vec4, vec4_out;   // (set by its launcher: aligned 16-byte accesses of a dense layer)
 };
 hipError_t launch_conv_f32(const ConvF32Params& p, hipStream_t s);
+// many pixels, few channels: launch_conv_f32 takes less time than the matrix-core kernel
+bool conv_f32_vector_faster(const ConvF32Params& p);
 // groups == 1, at most 32 taps, sizes within the index math: conv and dense on the fp32 matrix cores
 bool conv_f32_mfma_ok(const ConvF32Params& p);
 hipError_t launch_conv_f32_mfma(const ConvF32Params& p, hipStream_t s);

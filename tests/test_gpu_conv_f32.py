@@ -41,6 +41,7 @@ def _check(wl, terms, what):
             torch.cuda.synchronize()
             err = np.abs(runtime.to_host_f64(bufs[-1]) - ref)
             assert (err <= (terms + 3) * 2.0 ** -24 * np.abs(scale) + 1e-30).all(), (what, offset, float(err.max()))
+        return [l["name"] for l in sg.launches()]
 
 
 @pytest.mark.parametrize("case", CONVS, ids=["x".join(map(str, c[:5])) for c in CONVS])
@@ -49,7 +50,25 @@ def test_conv(case):
     g = GraphBuilder("f32_mfma", 5000 + CONVS.index(case), dtype="f32")
     x = g.input("x", [n, c, h, w], "normal")
     g.output(g.conv(x, k, r, stride=stride, pad=pad, act=act, residual=x if res else None, name="y"))
-    _check(g.finish(), c * r[0] * r[1], "conv %s" % (case,))
+    names = _check(g.finish(), c * r[0] * r[1], "conv %s" % (case,))
+    assert names == ["conv_f32_mfma" if r[0] * r[1] <= 32 else "conv_f32_direct"], names
+
+
+# many pixels and few channels: the register-blocked kernel (3x3 and 1x1) and the
+# direct one (other sizes), channels that do not fill a block of four, strides, residual
+FEW_CHANNELS = [(4, 3, 80, 81, 5, (3, 3), 1, 1, "relu", False), (2, 1, 301, 170, 1, (3, 3), 1, 1, None, False),
+                (7, 8, 121, 119, 8, (3, 3), 2, 1, "leaky", False), (1, 5, 190, 181, 5, (1, 1), 1, 0, "relu6", True),
+                (30, 4, 30, 31, 3, (1, 1), 1, 0, None, False), (3, 1, 160, 121, 3, (5, 5), 1, 2, "gelu", False),
+                (4, 3, 160, 121, 2, (1, 7), 1, [0, 3, 0, 3], "relu", False)]
+
+
+@pytest.mark.parametrize("case", FEW_CHANNELS, ids=["x".join(map(str, c[:5])) for c in FEW_CHANNELS])
+def test_few_channels_of_many_pixels(case):
+    n, c, h, w, k, r, stride, pad, act, res = case
+    g = GraphBuilder("f32_few_channels", 5050 + FEW_CHANNELS.index(case), dtype="f32")
+    x = g.input("x", [n, c, h, w], "normal")
+    g.output(g.conv(x, k, r, stride=stride, pad=pad, act=act, residual=x if res else None, name="y"))
+    assert _check(g.finish(), c * r[0] * r[1], "conv %s" % (case,)) == ["conv_f32_direct"]
 
 
 @pytest.mark.parametrize("case", DENSE, ids=["x".join(map(str, c[:3])) for c in DENSE])

@@ -374,10 +374,9 @@ def test_1x1_conv_of_padded_1x1_map(pad, stride):
 
 
 F32_CONV_CASES = [
-    # name, (n, c, h, w), k, r, stride, pad, act, residual: the
-    # register-blocked kernel (3x3 and 1x1: odd channel counts, output
-    # channels not a multiple of its 4-channel block, strides, residual) and
-    # the direct kernel (other kernel sizes)
+    # name, (n, c, h, w), k, r, stride, pad, act, residual: odd channel counts,
+    # strides, residual and asymmetric padding (the matrix-core kernel; the
+    # other fp32 kernels' cases are in test_gpu_conv_f32.py)
     ("s2_res_leaky_k13", (2, 64, 41, 40), 13, 3, 2, 1, "leaky", True),
     ("k5_asym_pad_direct", (1, 6, 23, 19), 20, 5, 1, (2, 0, 1, 3), "relu6", False),
     ("1x1_odd_channels", (1, 301, 9, 30), 16, 1, 1, 0, None, True),

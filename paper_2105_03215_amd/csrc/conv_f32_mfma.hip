@@ -11,7 +11,7 @@
 // registers.  8 x 128 x 28 x 28 by 128 channels 3x3: 86 us on vector FMAs with
 // scalar weights, 43 here; dense 300 x 768 x 2048 1989 -> 22, 30 rows 521 -> 8.4.
 //
-// M = output channels (weights [rows][ldw], kk = (c*R + r)*S + s, zero padded), N =
+// M = output channels (weights [K][ldw], kk = (c*R + r)*S + s, zero padded), N =
 // output pixels of all images.  LDS rows are kk-contiguous (stride + 4 floats: 8
 // consecutive rows start on 8 different bank groups), so a lane takes 4 elements of its
 // row per 16-byte read and the four MFMAs of 16 kk use element t of every
@@ -54,7 +54,9 @@ __global__ __launch_bounds__(64 * WM * WN * KG) void conv_f32_mfma_kernel(ConvF3
   // pixel rows like the weight rows)
   const int aq = tid % (BK / 4), ar = tid / (BK / 4);  // kk group, first row
   constexpr int AROWS = NT / (BK / 4);                 // rows per pass
-  const float* wa = p.w + (size_t)(k0 + ar) * p.ldw + aq * 4;
+  const float* wa[AQ];  // (rows past the last channel repeat it and are not stored)
+#pragma unroll
+  for (int i = 0; i < AQ; ++i) wa[i] = p.w + (size_t)min(k0 + ar + i * AROWS, p.K - 1) * p.ldw + aq * 4;
   // Images: a lane keeps its pixel's window origin and a bit per tap inside the
   // image; the offsets and bits of a stage's elements come from the table one
   // stage before its loads are issued (as vector loads: scalar ones share a
@@ -95,7 +97,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG) void conv_f32_mfma_kernel(ConvF3
     if (st >= nst) return;
     const int kb = st * BK;
 #pragma unroll
-    for (int i = 0; i < AQ; ++i) ra[U][i] = *(const f32x4*)(wa + (size_t)i * AROWS * p.ldw + kb);
+    for (int i = 0; i < AQ; ++i) ra[U][i] = *(const f32x4*)(wa[i] + kb);
     if constexpr (ROWS) {
 #pragma unroll
       for (int i = 0; i < BQ; ++i) {

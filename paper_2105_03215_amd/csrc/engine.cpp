@@ -1245,10 +1245,10 @@ void Planner::plan_node(int ni) {
       p.alpha = n.alpha;
       p.rows = R == 1 && S == 1 && H == 1 && W == 1 && P == 1 && Q == 1 && p.pt == 0 && p.pl == 0;
       if (conv_f32_mfma_ok(p) && !conv_f32_vector_faster(p)) {  // the matrix-core kernel, its weight rows padded
-        const int crs = Cg * R * S, rows = (int)rup(K, 64);
+        const int crs = Cg * R * S;
         p.ldw = (int)rup(crs, 256);
-        L.w = wslot((int64_t)rows * p.ldw * 4);
-        jobs.push_back({PackJob::RowsW32, wc, L.w.off, K, 0, 0, 0, 0, p.ldw, rows, crs, 0});
+        L.w = wslot((int64_t)K * p.ldw * 4);
+        jobs.push_back({PackJob::RowsW32, wc, L.w.off, K, 0, 0, 0, 0, p.ldw, 0, crs, 0});
         if (!p.rows) {
           std::vector<uint8_t> b((size_t)p.ldw * sizeof(F32Tap), 0);
           F32Tap* t = reinterpret_cast<F32Tap*>(b.data());
@@ -2498,7 +2498,7 @@ Status build_device_state(Engine* e, Planner& pl, const byoc_const* consts) {
           err = launch_pack_dw_weights_f32(src, sb, (float*)dst, j.K, j.R, j.S, j.Cp, nullptr);
           break;
         case PackJob::RowsW32:
-          err = launch_pack_rows_f32(src, sb, (float*)dst, j.K, j.n, j.Kgp, j.rows, nullptr);
+          err = launch_pack_rows_f32(src, sb, (float*)dst, j.K, j.n, j.Kgp, nullptr);
           break;
         case PackJob::Vec:
           err = launch_pack_vector_f32(src, sb, (float*)dst, j.n, j.n_out, nullptr);

@@ -249,7 +249,7 @@ struct F32Tap {
 };
 struct ConvF32Params {
   const float* x;
-  const float* w;  // OIHW [K][C/groups][R][S]; matrix-core kernel: the same rows padded to [rup(K, 64)][ldw] with zeros
+  const float* w;  // OIHW [K][C/groups][R][S]; matrix-core kernel: the same rows padded to ldw with zeros
   const float* bias;
   const float* res;  // NCHW like y, or nullptr
   float* y;
@@ -268,8 +268,7 @@ bool conv_f32_vector_faster(const ConvF32Params& p);
 // groups == 1, at most 32 taps, sizes within the index math: conv and dense on the fp32 matrix cores
 bool conv_f32_mfma_ok(const ConvF32Params& p);
 hipError_t launch_conv_f32_mfma(const ConvF32Params& p, hipStream_t s);
-hipError_t launch_pack_rows_f32(const void* src, bool src_bf16, float* dst, int K, int n, int ld, int rows,
-                                hipStream_t s);
+hipError_t launch_pack_rows_f32(const void* src, bool src_bf16, float* dst, int K, int n, int ld, hipStream_t s);
 
 // Depthwise conv NHWC bf16: weights packed [R*S][Cp] bf16, bias fp32 [Cp].
 struct DwParams {

@@ -464,13 +464,12 @@ __global__ __launch_bounds__(kThreads) void pack_dw_weights_f32_kernel(const Src
 }
 
 template <typename SrcT>
-__global__ __launch_bounds__(kThreads) void pack_rows_f32_kernel(const SrcT* src, float* dst, int K, int n, int ld,
-                                                                 int rows) {
+__global__ __launch_bounds__(kThreads) void pack_rows_f32_kernel(const SrcT* src, float* dst, int K, int n, int ld) {
   const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (idx >= (int64_t)rows * ld) return;
+  if (idx >= (int64_t)K * ld) return;
   const int c = (int)(idx % ld);
   const int64_t k = idx / ld;
-  dst[idx] = k < K && c < n ? load_f(src, (size_t)k * n + c) : 0.f;
+  dst[idx] = c < n ? load_f(src, (size_t)k * n + c) : 0.f;
 }
 
 template <typename SrcT>
@@ -696,13 +695,12 @@ hipError_t launch_pack_dw_weights_f32(const void* src, bool src_bf16, float* dst
   return hipGetLastError();
 }
 
-hipError_t launch_pack_rows_f32(const void* src, bool src_bf16, float* dst, int K, int n, int ld, int rows,
-                                hipStream_t s) {
-  const int64_t total = (int64_t)rows * ld;
+hipError_t launch_pack_rows_f32(const void* src, bool src_bf16, float* dst, int K, int n, int ld, hipStream_t s) {
+  const int64_t total = (int64_t)K * ld;
   if (src_bf16)
-    pack_rows_f32_kernel<bf16_t><<<grid_for(total), kThreads, 0, s>>>((const bf16_t*)src, dst, K, n, ld, rows);
+    pack_rows_f32_kernel<bf16_t><<<grid_for(total), kThreads, 0, s>>>((const bf16_t*)src, dst, K, n, ld);
   else
-    pack_rows_f32_kernel<float><<<grid_for(total), kThreads, 0, s>>>((const float*)src, dst, K, n, ld, rows);
+    pack_rows_f32_kernel<float><<<grid_for(total), kThreads, 0, s>>>((const float*)src, dst, K, n, ld);
   return hipGetLastError();
 }
 

@@ -118,3 +118,13 @@ def test_infinities_and_denormals():
         mid = out[0].double().cpu().numpy()[:, :, 1:-1, 1:-1]
         sg2.close()
         assert (mid == 360 * 2.0 ** -136).all(), mid.flat[0] / 2.0 ** -136
+
+
+def test_weights_are_not_padded_by_rows():
+    """A layer of one output holds about its weights (columns are padded to 256)."""
+    g = GraphBuilder("f32_one_output", 5400, dtype="f32")
+    g.output(g.dense(g.input("x", [3, 5000], "normal"), 1, name="y"))
+    wl = g.finish()
+    with capi.Subgraph(wl.graph, wl.consts, device=0) as sg:
+        assert [l["name"] for l in sg.launches()] == ["conv_f32_mfma"]
+        assert sg.stats()["weight_bytes"] <= 4 * 5120 + 1024

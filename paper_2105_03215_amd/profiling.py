@@ -137,7 +137,7 @@ def _copy_kib(path, counter):
 
 CONV_SOURCES = ("conv_mfma.hip", "conv_dma.hip", "conv_pipe.hip", "conv_few.hip", "conv_halo.hip", "bottleneck.hip", "ir_block.hip", "lds_dma.h",
                 "stem.hip", "dense_rows.hip", "engine.cpp")
-I8_KERNELS = ("conv_i8_kernel", "bottleneck_kernel", "conv_halo_kernel", "stem_conv_maxpool_kernel")
+I8_KERNELS = ("conv_i8_kernel", "conv_pipe_kernel", "bottleneck_kernel", "conv_halo_kernel", "stem_conv_maxpool_kernel")
 I8_SOURCES = ("conv_i8.hip", "conv_pipe.hip", "conv_halo.hip", "bottleneck.hip", "stem.hip", "quant.hip", "quant_epilogue.h", "lds_dma.h",
               "engine.cpp")
 

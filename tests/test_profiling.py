@@ -80,3 +80,19 @@ def test_traffic_scales_by_copy_calibration(tmp_path):
     assert doc["conv_fetch_bytes_per_step"] == 400 * 1024 * 2
     assert doc["conv_write_bytes_per_step"] == 400 * 1024 // 2
     assert json.loads(out.read_text())["runs_counted"] == 2
+
+
+def test_kernels_count_in_one_class():
+    """Kernels compiled for bf16 and for int8 codes: the int8 form counts in the int8
+    class alone, the other in the bf16 class alone."""
+    ns = "void byoc::(anonymous namespace)::"
+    for bf16, i8 in ((ns + "conv_pipe_kernel<128, 128, 2, 4, 2, false>(byoc::QConvParams)",
+                      ns + "conv_pipe_kernel<128, 128, 2, 4, 2, true>(byoc::QConvParams)"),
+                     (ns + "conv_halo_kernel<128, 64, 3, 4, 2, false>(byoc::QConvParams)",
+                      ns + "conv_halo_kernel<128, 64, 3, 4, 2, true>(byoc::QConvParams)"),
+                     (ns + "conv_few_kernel<1, 1, 4>(byoc::ConvParams)", ns + "conv_i8_kernel<64, 64, 3>(byoc::QConvParams)"),
+                     (ns + "grouped_conv_few_kernel<1, 1, 4>(byoc::ConvGroup)", None),
+                     (ns + "grouped_conv_dma_kernel<64, 64, 2, 2, 2, 3, true>(byoc::ConvGroup)", None)):
+        assert profiling._is_conv(bf16) and not profiling._is_conv(bf16, profiling.I8_KERNELS), bf16
+        if i8:
+            assert profiling._is_conv(i8, profiling.I8_KERNELS) and not profiling._is_conv(i8), i8

@@ -118,6 +118,11 @@ def _profile(sg, ins, outs, stream, steps):
     return [m / max(runs, 1) for m in ms], runs
 
 
+def _dispatches(launches):
+    from paper_2105_03215_amd import profiling
+    return profiling.dispatches(launches)
+
+
 def _roofline(launches, per_launch_ms, step_ms, traffic=None):
     """Roofline of the conv/dense MFMA class.  Its time per step is the
     timed step (HIP events around the timed steps) less the other
@@ -128,7 +133,7 @@ def _roofline(launches, per_launch_ms, step_ms, traffic=None):
     other_ms = sum(t for l, t in zip(launches, per_launch_ms) if l["kind"] not in conv_kinds)
     conv_ms = max(step_ms - other_ms, 1e-9)
     conv_flops = sum(l["flops"] for l in launches if l["kind"] == "conv_mfma")
-    n_conv = sum(1 for l in launches if l["kind"] == "conv_mfma")
+    n_conv = _dispatches([l for l in launches if l["kind"] == "conv_mfma"])
     achieved = conv_flops / (conv_ms * 1e-3) / 1e12
     # per-layer floor: each conv launch at its own roofline, max(flops / MFMA
     # peak, algorithmic bytes / HBM peak); the 1x1 layers are HBM-bound, so
@@ -138,7 +143,7 @@ def _roofline(launches, per_launch_ms, step_ms, traffic=None):
     return {"bound": "mfma", "achieved": round(achieved, 2), "peak": PEAK_BF16_TFLOPS,
             "unit": "TFLOP/s", "frac": round(achieved / PEAK_BF16_TFLOPS, 4),
             "traffic": traffic,
-            "kernel": ("conv/dense bf16 MFMA class (stem_conv_maxpool, conv_dma, conv_halo, conv_mfma, bottleneck, ir_block, dense_rows, "
+            "kernel": ("conv/dense bf16 MFMA class (stem_conv_maxpool, conv_dma, conv_pipe, conv_few, conv_halo, conv_mfma, bottleneck, ir_block, dense_rows, "
                        "splitk_reduce kernels), %d launches per step" % n_conv),
             "flops_per_step": conv_flops, "kernel_ms_per_step": round(conv_ms, 4),
             "per_launch_event_ms_per_step": round(conv_ev_ms, 4),
@@ -278,7 +283,7 @@ def _config_lines(args, dev, stream):
                      % (fl / 1e6, fl / (PEAK_F32_TFLOPS * 1e12) * 1e6, PEAK_F32_TFLOPS)},
         "launch_mode": m.extra["launch_mode"], "us_direct": round(m.extra["ms_direct"]["median"] * 1e3, 2),
         "us_graph": round(m.extra["ms_graph"]["median"] * 1e3, 2) if "ms_graph" in m.extra else None,
-        "launches": len(m.launches)}
+        "launches": _dispatches(m.launches)}
 
     m = _measure(args, "resnet18_block", workloads.build("resnet18_block"), dev, stream, timing="grouped")
     measured.append(m)
@@ -288,7 +293,7 @@ def _config_lines(args, dev, stream):
         "config": "ResNet-18 basic block, bf16, 1x64x56x56 (conv3x3+bias+ReLU, conv3x3+bias+residual+ReLU)",
         "us_per_block": round(m.ms * 1e3, 2), "us_p10_p90": [round(m.extra["ms"]["p10"] * 1e3, 2),
                                                              round(m.extra["ms"]["p90"] * 1e3, 2)],
-        "tflops": round(tf, 2), "mfma_frac": round(tf / PEAK_BF16_TFLOPS, 4), "launches": len(m.launches),
+        "tflops": round(tf, 2), "mfma_frac": round(tf / PEAK_BF16_TFLOPS, 4), "launches": _dispatches(m.launches),
         "launch_mode": m.extra["launch_mode"], "us_direct": round(m.extra["ms_direct"]["median"] * 1e3, 2),
         "us_graph": round(m.extra["ms_graph"]["median"] * 1e3, 2) if "ms_graph" in m.extra else None,
         "kernel_classes": _class_summary(m.launches, m.per_launch)}
@@ -300,7 +305,7 @@ def _config_lines(args, dev, stream):
         out["resnet50_v1_bs1"] = {
             "images_per_s": round(1.0 / (m.ms * 1e-3), 1), "ms_per_step": round(m.ms, 4),
             "ms_p10_p90": [m.extra["ms"]["p10"], m.extra["ms"]["p90"]],
-            "conv_tflops": round(fl / (m.ms * 1e-3) / 1e12, 2), "launches": len(m.launches),
+            "conv_tflops": round(fl / (m.ms * 1e-3) / 1e12, 2), "launches": _dispatches(m.launches),
             "launch_mode": m.extra["launch_mode"],
             "ms_direct": m.extra["ms_direct"]["median"], "ms_graph": m.extra.get("ms_graph", {}).get("median")}
 
@@ -312,7 +317,7 @@ def _config_lines(args, dev, stream):
         fl = sum(l["flops"] for l in m.launches if l["kind"] == "conv_mfma")
         out["mobilenet_v2_bs%d" % n] = {
             "images_per_s": round(n / (m.ms * 1e-3), 1), "ms_per_step": round(m.ms, 4),
-            "conv_tflops": round(fl / (m.ms * 1e-3) / 1e12, 2), "launches": len(m.launches),
+            "conv_tflops": round(fl / (m.ms * 1e-3) / 1e12, 2), "launches": _dispatches(m.launches),
             "launch_mode": m.extra["launch_mode"],
             "depthwise": ({k: cls["depthwise"][k] for k in ("launches", "ms", "bytes", "gbs", "hbm_frac")}
                           if "depthwise" in cls else
@@ -327,7 +332,7 @@ def _config_lines(args, dev, stream):
     out["bert_ffn"] = {
         "config": "BERT-base FFN x12, 1024 tokens (batch 8 x seq 128), hidden 768 -> 3072 (GELU) -> 768 + residual",
         "tokens_per_s": round(1024 / (m.ms * 1e-3), 1), "ms_per_step": round(m.ms, 4),
-        "tflops": round(tf, 2), "mfma_frac": round(tf / PEAK_BF16_TFLOPS, 4), "launches": len(m.launches),
+        "tflops": round(tf, 2), "mfma_frac": round(tf / PEAK_BF16_TFLOPS, 4), "launches": _dispatches(m.launches),
         "kernel_classes": _class_summary(m.launches, m.per_launch)}
     return out, measured
 
@@ -516,7 +521,7 @@ def _quantized(args, wl, dev, stream, calib_images=2, variant=None):
                                    "the windowed 3x3 kernel), %d launches per step"
                                    % sum(1 for l in launches if l["kind"] == "conv_i8"),
                          "ops_per_step": ops, "kernel_ms_per_step": round(conv_ms, 4)},
-            "kernel_classes": _class_summary(launches, per_launch), "launches": len(launches)}
+            "kernel_classes": _class_summary(launches, per_launch), "launches": _dispatches(launches)}
 
 
 def _other_workload(args, name, batch, dev, stream):
@@ -531,7 +536,7 @@ def _other_workload(args, name, batch, dev, stream):
     out = {"workload": m.key, "images_per_s": round(batch / (m.ms * 1e-3), 1),
            "ms_per_step": round(m.ms, 4), "launch_mode": m.extra["launch_mode"],
            "gflop_per_image": round(2 * wl.macs / batch / 1e9, 3),
-           "conv_tflops": roof["achieved"], "conv_frac": roof["frac"], "launches": len(m.launches)}
+           "conv_tflops": roof["achieved"], "conv_frac": roof["frac"], "launches": _dispatches(m.launches)}
     if not args.no_quantized:  # the same network partially quantized, as the headline's int8 leg
         try:
             q = _quantized(args, wl, dev, stream, variant=name)
@@ -688,7 +693,7 @@ def main():
         "data": "synthetic (seeded uniform[0,1) images, random He-init weights with folded BN)",
         "config": {"workload": "%s_bs%d" % (args.variant, args.batch), "batch": args.batch,
                    "input": list(wl.inputs[0].shape), "gflop_per_image": round(2 * wl.macs / args.batch / 1e9, 3),
-                   "launches_per_step": len(launches), "parallelism": "none (1 GPU)",
+                   "launches_per_step": _dispatches(launches), "parallelism": "none (1 GPU)",
                    "launch_mode": mode},
         "eager_images_per_s": round(args.batch / (ms_eager * 1e-3), 1),
         "graph_images_per_s": round(args.batch / (ms_graph * 1e-3), 1),

@@ -137,7 +137,11 @@ typedef enum {
   BYOC_K_CONV_I8 = 8    /* implicit-GEMM conv / dense on int8 MFMA      */
 } byoc_kernel_kind;
 
-/* One entry of the launch sequence a run enqueues. */
+/* One entry of the launch sequence a run enqueues.  Independent convolutions
+ * that go out together in one device launch have an entry each, one after the
+ * other, with names that end in _g<place>/<members> ("..._g1/3"): the run enqueues as
+ * many device launches as there are entries without such an ending or with
+ * place 1. */
 typedef struct {
   int32_t kind;       /* byoc_kernel_kind                                   */
   int32_t node;       /* index of the JSON node, -1 for boundary transforms */
@@ -218,16 +222,18 @@ byoc_status byoc_subgraph_io_desc(const byoc_subgraph* g, int32_t is_output, int
 byoc_status byoc_subgraph_stats(const byoc_subgraph* g, int64_t* macs, int64_t* weight_bytes,
                                 int64_t* arena_bytes);
 
-/* Number of device launches one run enqueues, and their descriptions. */
+/* Number of entries of a run's launch sequence (byoc_launch_info: a device
+ * launch each, but for the members of a group), and their descriptions. */
 byoc_status byoc_subgraph_num_launches(const byoc_subgraph* g, int32_t* n);
 byoc_status byoc_subgraph_launch_info(const byoc_subgraph* g, int32_t i, byoc_launch_info* info);
 
 /* Per-launch timing.  byoc_subgraph_profile_begin(g, max_runs) allocates
  * HIP events for max_runs runs; each following run records an event on its
- * stream before its first launch and after every launch.  profile_end
+ * stream before its first launch and after every device launch.  profile_end
  * synchronises on the last recorded event, writes into ms[i] (n >= number
- * of launches) the summed duration of launch i over the recorded runs,
- * stores that run count in *runs, and frees the events.  Runs past
+ * of entries) the summed duration of entry i over the recorded runs - of a
+ * group's members each one's share of their device launch by its flops, which is no
+ * measurement of its own -, stores that run count in *runs, and frees the events.  Runs past
  * max_runs are not recorded. */
 byoc_status byoc_subgraph_profile_begin(byoc_subgraph* g, int32_t max_runs);
 byoc_status byoc_subgraph_profile_end(byoc_subgraph* g, float* ms, int32_t n, int32_t* runs);

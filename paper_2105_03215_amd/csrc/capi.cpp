@@ -1,4 +1,5 @@
 // The extern "C" boundary of include/byoc.h.
+#include <cstdio>
 #include <cstring>
 #include <new>
 #include <string>
@@ -132,7 +133,15 @@ byoc_status byoc_subgraph_launch_info(const byoc_subgraph* g, int32_t i, byoc_la
   if (!g || !g->engine || !info) return fail(BYOC_ERR_INVALID_ARG, "NULL argument");
   if (i < 0 || i >= (int32_t)g->engine->launches.size())
     return fail(BYOC_ERR_INVALID_ARG, "launch index out of range");
-  *info = g->engine->launches[i].info;
+  const std::vector<byoc::Launch>& launches = g->engine->launches;
+  *info = launches[i].info;
+  // a member of a group says so: the kernel name ends in _g<place>/<members>
+  for (int32_t first = i; first >= 0 && first > i - byoc::kConvGroup; --first)
+    if (launches[first].group > i - first) {
+      const size_t len = std::strlen(info->name);
+      std::snprintf(info->name + len, sizeof(info->name) - len, "_g%d/%d", i - first + 1, launches[first].group);
+      break;
+    }
   return BYOC_OK;
 }
 

@@ -37,6 +37,7 @@ import csv
 import hashlib
 import json
 import os
+import re
 import statistics
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -47,6 +48,12 @@ RUN_MARKER = "stem_conv_maxpool_kernel"  # one dispatch per run of the ResNet su
 # kernels compiled for bf16 and for int8 codes: the int8 form has `true` as
 # its last template argument
 DUAL_KERNELS = ("bottleneck_kernel", "conv_halo_kernel", "conv_pipe_kernel", "stem_conv_maxpool_kernel")
+
+
+def dispatches(launches):
+    """Device launches of a run: members of a group after its first (names
+    ending in _g<place>/<members>) go out with it."""
+    return sum(1 for l in launches if not re.search(r"_g([2-9]|\d\d+)/\d+$", l["name"]))
 
 
 def _short(name):
@@ -302,7 +309,7 @@ def run_workload(name, batch, runs, warmup, autotune=True):
         launches = sg.launches()
     finally:
         sg.close()
-    return {"workload": name, "batch": batch, "runs": runs, "launches_per_run": len(launches),
+    return {"workload": name, "batch": batch, "runs": runs, "launches_per_run": dispatches(launches),
             "flops_per_run": sum(l["flops"] for l in launches), "launches": [l["name"] for l in launches]}
 
 

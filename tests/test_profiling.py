@@ -96,3 +96,9 @@ def test_kernels_count_in_one_class():
         assert profiling._is_conv(bf16) and not profiling._is_conv(bf16, profiling.I8_KERNELS), bf16
         if i8:
             assert profiling._is_conv(i8, profiling.I8_KERNELS) and not profiling._is_conv(i8), i8
+
+
+def test_dispatches_count_a_group_once():
+    names = ["nchw_to_nhwc", "conv_few_16x16_k4_w4_g1/3", "conv_few_16x16_k8_w8_g2/3", "conv_few_16x16_k1_w1_g3/3",
+             "conv_dma_64x64_s3_w8_k2_split1", "conv_dma_64x64_s3_w8_k2_split1_g1/2", "conv_dma_64x64_s3_w8_k2_split1_g2/2"]
+    assert profiling.dispatches([{"name": n} for n in names]) == 4

@@ -102,3 +102,25 @@ def test_members_name_their_group():
     members = sum(int(names[i].rsplit("/", 1)[1]) for i in heads)
     assert sum("_g" in n for n in names) == members
     assert profiling.dispatches([{"name": n} for n in names]) == len(names) - members + len(heads)
+
+
+@pytest.mark.parametrize("branches", [3, 12])
+def test_order_that_fits_the_static_scratch_stays(branches):
+    """Branches of an 8 MiB map each: side by side, twelve of them need more than the
+    static scratch, one after the other they do not, so their order stays and run_static works."""
+    g = GraphBuilder("group_scratch", 7200)
+    x = g.input("x", [1, 64, 256, 256])
+    for _ in range(branches):
+        g.output(g.conv(g.conv(x, 64, 1, act="relu"), 64, 1, stride=8, pad=0, act=None))
+    wl = g.finish()
+    announce("group order and the static scratch, %d branches" % branches)
+    with capi.Subgraph(wl.graph, wl.consts, device=0) as sg:
+        assert sg.stats()["arena_bytes"] <= 64 << 20
+        assert any("_g1/" in l["name"] for l in sg.launches()) == (branches == 3), [l["name"] for l in sg.launches()]
+        ins = runtime.inputs_for(sg, wl.inputs, DEV)
+        outs = [runtime.outputs_for(sg, DEV) for _ in range(2)]
+        sg.run(ins, outs[0])
+        sg.run_static(ins, outs[1])
+        torch.cuda.synchronize()
+    for a, b in zip(*outs):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))

@@ -2748,14 +2748,19 @@ std::vector<ConvTile> conv_candidates(const Launch& L) {
   const ConvParams& p = L.conv;
   const int kgr = L.tile_default.kgroups;  // the reduction order class of the built-in choice
   if (kgr == 1 && conv_pipe_ok(p)) {
-    // conv_pipe's tiles, the pipelined kernel's that win where an epilogue or
-    // a residual weighs most, and the register-staged kernel: all sum in one order
+    // conv_pipe's tiles, the pipelined kernel's that were fastest for some layer of
+    // the networks (among all of its single-group tiles; tuning over all takes twice as long
+    // as over these), and the register-staged kernel: all sum in one order.  Eight waves on
+    // 128x64 and four on 128x128 take a fifth of DarkNet-53's layers at batch 32 (1.205 ms a
+    // step without them, 1.165 with all).
     pipe_tiles();
     struct D {
       int bm, bn, st, th;
     };
-    for (const D& d : {D{128, 128, 2, 512}, D{128, 128, 3, 512}, D{128, 128, 1, 512}, D{128, 64, 4, 512}, D{128, 64, 2, 256}, D{64, 64, 2, 256},
-                       D{64, 64, 3, 256}, D{64, 64, 4, 256}, D{64, 128, 2, 256}, D{32, 64, 3, 256}, D{32, 64, 4, 256}}) {
+    for (const D& d : {D{128, 128, 2, 512}, D{128, 128, 3, 512}, D{128, 128, 1, 512}, D{128, 128, 4, 512}, D{128, 128, 2, 256},
+                       D{128, 64, 4, 512}, D{128, 64, 3, 512}, D{128, 64, 2, 512}, D{128, 64, 1, 512}, D{128, 64, 2, 256},
+                       D{64, 64, 1, 256}, D{64, 64, 2, 256}, D{64, 64, 3, 256}, D{64, 64, 4, 256}, D{64, 128, 2, 256},
+                       D{64, 128, 3, 512}, D{64, 128, 4, 512}, D{32, 64, 3, 256}, D{32, 64, 4, 256}}) {
       if (d.bm == 32 && p.M >= 48) continue;
       if (d.bn == 128 && p.Kp < 128) continue;
       ConvTile t;

@@ -212,7 +212,7 @@ __global__ __launch_bounds__(64 * NW) void grouped_conv_few_kernel(ConvGroup g) 
 // one, so beyond that four with two segments or more each (192 -> 192 1x7 at
 // 17x17, 5 segments, 30 workgroups per XCD: 9.9 us on eight waves, 8.9 on four).
 int waves_of(int segs, int per_xcd) {
-  return segs <= 1 ? 1 : segs <= 2 ? 2 : segs <= 4 || per_xcd > kXcdSlots ? 4 : 8;
+  return segs <= 1 ? 1 : segs <= 4 || per_xcd > kXcdSlots ? 4 : 8;
 }
 
 template <int TM, int TN, int NW>
@@ -231,7 +231,6 @@ hipError_t launch_tile(ConvGroup& g, int n, hipStream_t s) {
   for (int i = 0; i < n; ++i) segs = std::max(segs, g.p[i].few_segs);
   switch (waves_of(segs, (int)(grid.x + 7) / 8 * n)) {
     case 1: return launch_waves<TM, TN, 1>(g, n, segs, grid, s);
-    case 2: return launch_waves<TM, TN, 2>(g, n, segs, grid, s);
     case 4: return launch_waves<TM, TN, 4>(g, n, segs, grid, s);
     default: return launch_waves<TM, TN, 8>(g, n, segs, grid, s);
   }

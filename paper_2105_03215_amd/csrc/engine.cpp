@@ -1377,8 +1377,10 @@ void Planner::plan_node(int ni) {
     p.splits = splits;
     p.k_tiles_per_split = kps;
     const bool builtin = !std::getenv("BYOC_CONV_TILE") && !std::getenv("BYOC_CONV_SPLIT");
-    // few 64x64 tiles: conv_few, where its modelled time is less
-    if (builtin && ((p.M + 63) / 64) * (int64_t)((Kp + 63) / 64) <= 64) {
+    // few 64x64 tiles: conv_few, where its modelled time is less.  Not for
+    // two reduction groups, whose halves are too long for a wave each (1024 -> 512 1x1 at
+    // 7x7, batch 8, with events: 8.8 us against 8.0 on the pipelined kernel).
+    if (builtin && L.tile.kgroups != 2 && ((p.M + 63) / 64) * (int64_t)((Kp + 63) / 64) <= 64) {
       ConvTile t{};
       if (conv_few_ok(few) && choose_few_tile(few, &t) < few_tiles_cost(L.tile, splits, kps, p.Kg)) {
         L.tile = t;

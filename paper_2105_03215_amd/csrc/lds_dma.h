@@ -101,8 +101,11 @@ inline int placed_blocks(ConvParams& p, int bm, int bn) {
   return ntm * ntn;
 }
 
-// Workgroups of one per CU that an XCD takes at once: with 29 per XCD (1x7 convs
-// of 160 channels, 231 tiles) 10.1 us, with 31 (246 tiles) 15.9, although it has 32 CUs.
+// Workgroups of one per CU that an XCD is sure to take at once, although it has 32 CUs:
+// 1x7 convs of 160 channels with 29 per XCD (231 tiles) 10.1 us, with 31 (246 tiles) 15.9; the
+// windowed 3x3 kernel with 28 at 256 channels 16.6, with 31 18.6.  It decides where
+// a second workgroup per CU is made room for (ring stages of grouped convs, waves of
+// conv_few); the tile-time model counts 32, and its fit holds the difference as scatter.
 constexpr int kXcdSlots = 29;
 
 // Several convs in one launch: a grid row of workgroups per conv, as long as the

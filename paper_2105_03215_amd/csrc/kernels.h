@@ -38,7 +38,6 @@ struct ConvParams {
   int w_bytes;
   int res_bytes;
   int res_post;  // 1: the residual is added after the activation, to its bf16-rounded value
-  int few_segs;  // conv_few: accumulators of an output (of k_tiles_per_split steps each, or 0: interleaved)
   int slice_major;  // conv_pipe: 1 sums 64-channel slices outermost, taps inside (conv_halo's order), 0 taps outermost
   // conv_dma tile placement: > 0 splits the tile grid into (8 / xcd_py) x
   // xcd_py blocks along (pixels, channels), one per XCD, so that an XCD's L2
@@ -50,7 +49,13 @@ struct ConvParams {
   // launchers (the tile divisor depends on the tile shape).
   uint64_t mg_pq, mg_q, mg_cp, mg_s;
   uint64_t mg_tile;  // divisor: channel tiles per row of the tile grid (or per XCD block)
-  uint64_t mg_wp, mg_hp;  // conv_halo: divisors W + 2 and H + 2 (set by its launcher)
+  // (one place for both: a field more changes the argument loads, and with them the
+  // register allocation, of every kernel that takes these parameters)
+  union {
+    uint64_t mg_wp;  // conv_halo: divisor W + 2 (set by its launcher)
+    int few_segs;    // conv_few: accumulators of an output (k_tiles_per_split steps each; 0: interleaved)
+  };
+  uint64_t mg_hp;  // conv_halo: divisor H + 2 (set by its launcher)
 };
 
 // independent convs of one launch, on the same tile
